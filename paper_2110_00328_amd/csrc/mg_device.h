@@ -89,6 +89,15 @@ __device__ __forceinline__ float f_sqrt(float x) { return __builtin_amdgcn_sqrtf
 __device__ __forceinline__ float f_rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ float f_div(float a, float b) { return a * f_rcp(b); }
 
+// A product that is never fused into a following add.  The FP32 cell updates
+// state which products are fused (fused multiply-adds below) and which are
+// not, so that every kernel form of a level operation, whatever it keeps in
+// registers or hoists out of its loops, rounds the same way.
+__device__ __forceinline__ float mul_nc(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
 // Root of t^3 + p t + q = 0 on the branch the paper's closed forms select:
 // the single real root, else the largest of three (for q < 0: the unique
 // positive root).  Viete's trigonometric/hyperbolic forms -- Cardano's form
@@ -319,43 +328,48 @@ __device__ __forceinline__ void cq_corr_terms(const Consts& C, float x, float e,
   *dnp = -C.f_cq_src * dsrc - C.f_cq_pot * a1 * ict2 * (PX * iY) * (1.0f + E2) * f_rcp(1.0f + u);
 }
 
-// Nonlinear part N(x+e) - N(x) of each model, accurate relative to e.
+// Symmetron: (1 + delta) a_*^3/a^3 - 1 + 3 x^2
+__device__ __forceinline__ float sym_mass(const Consts& C, float x, float dc) {
+  return __fmaf_rn(x, mul_nc(3.0f, x), __fmaf_rn(C.f_s_ratio, 1.0f + dc, -1.0f));
+}
+// G_c(e) = F(x+e)_c - F(x)_c: F = -kap Lap + N (f(R)), +kap Lap + N
+// (symmetron, CQ), with the change of the nonlinear part N written accurate
+// relative to e.
 template <int M>
-__device__ __forceinline__ float corr_nl(const Consts& C, float e, float x, float dc) {
+__device__ __forceinline__ float corr_G(const Consts& C, float h2, float ec, float sum, float x,
+                                        float dc) {
+  const float lap = mul_nc(__fmaf_rn(ec, -6.0f, sum), 1.0f / h2);  // h2 = 4^l: exact
   if constexpr (M == FR) {
     // K wbar^m [x^{-m} - (x+e)^{-m}] = A [1 - (1+t)^{-m}], m = 1/(n+1),
     // t = e/x, A = K wbar^m x^{-m}; written without cancellation:
     //   n = 0: A t/(1+t);  n = 1: A t/(s(1+s)), s = sqrt(1+t);
     //   n = 2: A t/(c(c^2+c+1)), c = cbrt(1+t)
-    float ix = f_rcp(x);
-    float t = e * ix;
+    const float ix = f_rcp(x);
+    const float t = mul_nc(ec, ix), t1 = __fmaf_rn(ec, ix, 1.0f);
+    float a, r;  // N = a r
     if (C.fr_n == 1) {
-      float s = f_sqrt(1.0f + t);
-      return C.f_kw * f_rsq(x) * t * f_rcp(s * (1.0f + s));
+      const float s = f_sqrt(t1);
+      a = mul_nc(mul_nc(C.f_kw, f_rsq(x)), t);
+      r = f_rcp(mul_nc(s, 1.0f + s));
+    } else if (C.fr_n == 0) {
+      a = mul_nc(mul_nc(C.f_kw, ix), t);
+      r = f_rcp(t1);
+    } else {
+      const float c = cbrtf(t1);
+      a = mul_nc(mul_nc(C.f_kw, f_rcp(cbrtf(x))), t);
+      r = f_rcp(mul_nc(c, __fmaf_rn(c + 1.0f, c, 1.0f)));
     }
-    if (C.fr_n == 0) return C.f_kw * ix * t * f_rcp(1.0f + t);
-    float c = cbrtf(1.0f + t);
-    return C.f_kw * f_rcp(cbrtf(x)) * t * f_rcp(c * ((c + 1.0f) * c + 1.0f));
+    return __fmaf_rn(a, r, -mul_nc(C.f_ct2, lap));
   } else if constexpr (M == SYM) {
     // -s_amp [ (rho a*^3/a^3 - 1 + 3x^2) e + 3x e^2 + e^3 ]
-    float m = (1.0f + dc) * C.f_s_ratio - 1.0f + 3.0f * x * x;
-    return -C.f_s_amp * (m + (3.0f * x + e) * e) * e;
+    const float m = sym_mass(C, x, dc);
+    const float nl = mul_nc(ec, mul_nc(C.f_s_amp, __fmaf_rn(ec, __fmaf_rn(x, 3.0f, ec), m)));
+    return __fmaf_rn(C.f_ct2, lap, -nl);
   } else {
     float dn, dnp;
-    cq_corr_terms(C, x, e, dc, &dn, &dnp);
-    return dn;
+    cq_corr_terms(C, x, ec, dc, &dn, &dnp);
+    return (sum - 6.0f * ec) * (1.0f / h2) + dn;
   }
-}
-
-// Laplacian coefficient kappa of each model: F = -kap Lap (f(R)), +kap Lap
-// (symmetron, CQ); the sign is folded into corr_G.
-template <int M>
-__device__ __forceinline__ float corr_G(const Consts& C, float h2, float ec, float sum, float x,
-                                        float dc) {
-  float lap = (sum - 6.0f * ec) * (1.0f / h2);  // h2 = 4^l: exact
-  if constexpr (M == FR) return -C.f_ct2 * lap + corr_nl<M>(C, ec, x, dc);
-  else if constexpr (M == SYM) return C.f_ct2 * lap + corr_nl<M>(C, ec, x, dc);
-  else return lap + corr_nl<M>(C, ec, x, dc);
 }
 
 // Exact per-cell solve of G_c(e) = rho with the neighbours fixed.
@@ -372,9 +386,11 @@ __device__ __forceinline__ float corr_update(const Consts& C, float h2, float ec
     float iD = h2 * C.f_i6ct2;  // h^2 / (6 c^2), a level constant
     float ix = f_rcp(x);
     float xm = n == 1 ? ix * f_rsq(x) : (n == 0 ? ix * ix : ix * cbrtf(ix));  // x^{-(m+1)}
-    float beta = C.f_kw * iD * xm;
-    float gamma = (rho * iD + sum * (1.0f / 6.0f)) * ix;
-    float c1 = float(n + 1) + beta - gamma;
+    const float kwD = C.f_kw * iD;
+    const float rs = __fmaf_rn(sum, 1.0f / 6.0f, mul_nc(rho, iD));
+    float beta = mul_nc(kwD, xm);
+    float gamma = mul_nc(rs, ix);
+    float c1 = __fmaf_rn(-ix, rs, __fmaf_rn(kwD, xm, float(n + 1)));
     float sg;
     if (fabsf(gamma) < 1e-2f * c1) {
       sg = f_div(gamma, c1);  // small correction: linear guess, Newton below
@@ -388,9 +404,9 @@ __device__ __forceinline__ float corr_update(const Consts& C, float h2, float ec
     if (n == 1) {
 #pragma unroll
       for (int it = 0; it < 2; ++it) {
-        float f = ((sg + 3.0f) * sg + c1) * sg - gamma;
-        float fp = (3.0f * sg + 6.0f) * sg + c1;
-        sg -= f_div(f, fp);
+        const float f = __fmaf_rn(__fmaf_rn(sg + 3.0f, sg, c1), sg, -gamma);
+        const float fp = __fmaf_rn(__fmaf_rn(3.0f, sg, 6.0f), sg, c1);
+        sg = __fmaf_rn(-f, f_rcp(fp), sg);
       }
       return x * sg * (sg + 2.0f);
     }
@@ -414,24 +430,23 @@ __device__ __forceinline__ float corr_update(const Consts& C, float h2, float ec
     // e^3 + 3x e^2 + P e + Q = 0, P = m + 6 kap, Q = rho/s_amp - kap sum,
     // m = (1+delta) a*^3/a^3 - 1 + 3x^2, kap = c^2/(s_amp h^2)
     float kap = C.f_ct2_samp * (1.0f / h2);
-    // 6 kap is a level constant: added with explicit rounding so that no
-    // kernel fuses it into the sum and another not
-    float P = __fadd_rn((1.0f + dc) * C.f_s_ratio - 1.0f + 3.0f * x * x, __fmul_rn(6.0f, kap));
-    float Q = rho * C.f_isamp - kap * sum;
+    const float x3 = mul_nc(3.0f, x);
+    const float P = sym_mass(C, x, dc) + mul_nc(6.0f, kap);
+    const float Q = __fmaf_rn(rho, C.f_isamp, -mul_nc(kap, sum));
     float e;
     if (P > 0.0f && fabsf(Q) < 1e-2f * P * fabsf(x)) {
       e = f_div(-Q, P);
     } else {
       // total field y = x + e solves y^3 + p y + q = 0 (paper's branch)
-      float p = P - 3.0f * x * x;
-      float q = (2.0f * x * x - P) * x + Q;
+      float p = P - mul_nc(x, x3);
+      float q = __fmaf_rn(x, __fmaf_rn(x, x + x, -P), Q);
       e = (q < 0.0f ? cubic_root_approx(p, q) : cubic_root<float>(p, q)) - x;
     }
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
-      float g = ((e + 3.0f * x) * e + P) * e + Q;
-      float gp = (3.0f * e + 6.0f * x) * e + P;
-      if (gp != 0.0f) e -= f_div(g, gp);
+      const float g = __fmaf_rn(e, __fmaf_rn(e, e + x3, P), Q);
+      const float gp = __fmaf_rn(e, __fmaf_rn(e, 3.0f, mul_nc(6.0f, x)), P);
+      if (gp != 0.0f) e = __fmaf_rn(-g, f_rcp(gp), e);
     }
     return e;
   } else {
@@ -457,14 +472,17 @@ __device__ __forceinline__ void corr_update4(const Consts& C, float h2, const fl
   if constexpr (M == FR) {
     if (C.fr_n == 1) {
       const float iD = h2 * C.f_i6ct2;
+      const float kwD = C.f_kw * iD;
       float gamma[4], c1[4], sg[4], beta[4];
       bool big = false;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const float ix = f_rcp(x[q]);
-        beta[q] = C.f_kw * iD * (ix * f_rsq(x[q]));
-        gamma[q] = (rho[q] * iD + sum[q] * (1.0f / 6.0f)) * ix;
-        c1[q] = 2.0f + beta[q] - gamma[q];
+        const float xm = ix * f_rsq(x[q]);
+        const float rs = __fmaf_rn(sum[q], 1.0f / 6.0f, mul_nc(rho[q], iD));
+        beta[q] = mul_nc(kwD, xm);
+        gamma[q] = mul_nc(rs, ix);
+        c1[q] = __fmaf_rn(-ix, rs, __fmaf_rn(kwD, xm, 2.0f));
         sg[q] = f_div(gamma[q], c1[q]);
         big |= !(fabsf(gamma[q]) < 1e-2f * c1[q]);
       }
@@ -478,9 +496,9 @@ __device__ __forceinline__ void corr_update4(const Consts& C, float h2, const fl
       for (int it = 0; it < 2; ++it)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const float f = ((sg[q] + 3.0f) * sg[q] + c1[q]) * sg[q] - gamma[q];
-          const float fp = (3.0f * sg[q] + 6.0f) * sg[q] + c1[q];
-          sg[q] -= f_div(f, fp);
+          const float f = __fmaf_rn(__fmaf_rn(sg[q] + 3.0f, sg[q], c1[q]), sg[q], -gamma[q]);
+          const float fp = __fmaf_rn(__fmaf_rn(3.0f, sg[q], 6.0f), sg[q], c1[q]);
+          sg[q] = __fmaf_rn(-f, f_rcp(fp), sg[q]);
         }
 #pragma unroll
       for (int q = 0; q < 4; ++q) out[q] = x[q] * sg[q] * (sg[q] + 2.0f);

@@ -203,6 +203,17 @@ __global__ __launch_bounds__(kFusedThreads) void kg_fused(const GBox* __restrict
   fused_corr_body<M>(B.F, P, B.C, sh);
 }
 
+template <int M>
+__global__ __launch_bounds__(kFusedThreads) void kg_small(const GBox* __restrict__ tab,
+                                                          const GCtl* __restrict__ ctl, int it,
+                                                          FusedProg P) {
+  extern __shared__ __align__(16) unsigned char small_lds[];
+  __shared__ double sh[48];
+  if (it >= ctl[blockIdx.x].kb) return;
+  const GBox& B = tab[blockIdx.x];
+  small_cycle(B.F, P, SmallCorr<M>{B.C}, reinterpret_cast<float*>(small_lds), sh);
+}
+
 // packed master -> natural field
 template <int M>
 __global__ __launch_bounds__(kBlock) void kg_unpack(const GBox* __restrict__ tab) {

@@ -2457,7 +2457,6 @@ struct FusedLin {
   T* dg[kMaxFused];
   T* r[kMaxFused];
 };
-
 constexpr int kFusedThreads = 1024;
 
 template <int M, typename T, typename TD>
@@ -2650,6 +2649,450 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_lin(FusedLin<T> F, Fuse
       __syncthreads();
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// The same program with every level's arrays in LDS, for hierarchies whose
+// first fused level has n <= 16.  Their operations are short dependent phases
+// on at most 4096 cells, run by one workgroup, so what counts is the latency
+// of a phase and the instructions a cell takes: on global memory each phase
+// waits for L2 and decodes its indices again.  Here a thread owns the packed
+// positions tid and tid + 1024 of a level (in both colours: they share j, k
+// and their neighbours' places), works out their neighbours once per
+// operation and keeps the cells' coefficients in registers over the sweeps;
+// the residual of the restriction is formed per fine cell by all threads;
+// the coarse correction is laid out in natural order, where its corners
+// differ by constants; and a coarsest level of at most 10^3 has one cell per
+// thread, 4^3 on one wave, which needs no barrier.  A launch at 16^3, 8^3, 4^3
+// (8 coarsest sweeps) takes 26 us (f(R)), 31 (CQ), 43 (symmetron), 21 (linear,
+// FP32) and 42 (f(R), FP64) against 41, 52, 63, 38 and 94 on global memory; a
+// coarsest 10^3 in FP64 (200 sweeps) 330 against 761.  What bounds it now is
+// the dependent chain of a phase and, on 16^3, one compute unit's issue rate.
+// Larger coarsest levels (18^3, 22^3, ...) stay with the kernels above.
+// ---------------------------------------------------------------------------
+constexpr int kSmallN = 16;
+constexpr int kSmallQ = 2;  // positions per thread: kSmallN^3 / 2 <= kSmallQ kFusedThreads
+// a coarsest level of at most this many cells per colour has one cell per
+// thread, and is swept by one wave, without barriers, up to 32
+constexpr int kSmallSplit = kFusedThreads / 2;
+
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// one packed position: its own place and its neighbours' in the other
+// colour's array (x: the own place and xe[colour])
+struct SmallPos {
+  bool ok;
+  int ih, j, k, s0;  // s0 = (j + k) & 1
+  int g, xe[2], ym, yp, zm, zp;
+};
+__device__ __forceinline__ SmallPos small_pos(const Lev& L, int g) {
+  SmallPos p;
+  p.ok = g < (int)L.half;
+  p.g = p.ok ? g : 0;
+  dec(p.g, L, p.ih, p.j, p.k);
+  p.s0 = (p.j + p.k) & 1;
+  const int r = p.g - p.ih, pl = L.n * L.nh;
+  const int xm = r + (p.ih == 0 ? L.nh - 1 : p.ih - 1), xp = r + (p.ih + 1 == L.nh ? 0 : p.ih + 1);
+  p.xe[0] = p.s0 ? xp : xm;
+  p.xe[1] = p.s0 ? xm : xp;
+  p.ym = p.j == 0 ? p.g + pl - L.nh : p.g - L.nh;
+  p.yp = p.j == L.n - 1 ? p.g - pl + L.nh : p.g + L.nh;
+  p.zm = p.k == 0 ? p.g + pl * (L.n - 1) : p.g - pl;
+  p.zp = p.k == L.n - 1 ? p.g - pl * (L.n - 1) : p.g + pl;
+  return p;
+}
+// neighbour sum of the colour's cell, o: the other colour's array (nbsum's order)
+template <typename T>
+__device__ __forceinline__ T small_sum(const SmallPos& p, const T* o, int colour) {
+  return (o[p.g] + o[colour ? p.xe[1] : p.xe[0]]) + (o[p.ym] + o[p.yp]) + (o[p.zm] + o[p.zp]);
+}
+
+// What the three level problems put into a cell: coef (the linearisation
+// point X, or dg), right-hand side, density; the per-cell update and residual
+// are those of the kernels above.
+template <typename T>
+struct SmallCell {
+  T a, b, d;
+};
+// N: the Hu-Sawicki exponent when known at compile time (1, the usual one),
+// else -1: a launch runs every instruction but a few times, from a cold
+// instruction cache, so the code of the other exponents is left out
+template <int M, int N>
+__device__ __forceinline__ Consts small_consts(const Consts& c) {
+  Consts r = c;
+  if (M == FR && N >= 0) r.fr_n = N;
+  return r;
+}
+template <int M>
+struct SmallCorr {
+  typedef float T;
+  typedef FusedCorr F;
+  static constexpr bool kA = true, kD = M != FR, kR = true, kOld = M == CQ, kMean = M == CQ;
+  Consts C;
+  __device__ __forceinline__ static float par(const F& f, int l) { return f.h2[l]; }
+  __device__ __forceinline__ static float* U(const F& f, int l) { return f.e[l]; }
+  __device__ __forceinline__ static const float* A(const F& f, int l) { return f.X[l]; }
+  __device__ __forceinline__ static const float* B(const F& f, int l) { return f.rho[l]; }
+  __device__ __forceinline__ static const float* D(const F& f, int l) { return f.dens[l]; }
+  __device__ __forceinline__ float update(float h2, const SmallCell<T>& c, float old,
+                                          float sum) const {
+    return corr_update<M>(C, h2, old, sum, c.a, c.d, c.b);
+  }
+  __device__ __forceinline__ float resid(float h2, const SmallCell<T>& c, float u,
+                                         float sum) const {
+    return corr_G<M>(C, h2, u, sum, c.a, c.d) - c.b;
+  }
+  __device__ __forceinline__ double diag(float h2, const SmallCell<T>& c, float u) const {
+    return double(corr_diag<M>(C, h2, u, c.a, c.d)) + 6.0 / double(h2);
+  }
+  __device__ __forceinline__ static float mu(double D, double J) { return float(-D / J); }
+};
+template <int M>
+struct SmallDirect {
+  typedef double T;
+  typedef FusedDirect<double, double> F;
+  static constexpr bool kA = false, kD = true, kR = true, kOld = M == CQ, kMean = M == CQ;
+  Consts C;
+  __device__ __forceinline__ static double par(const F& f, int l) { return f.h2[l]; }
+  __device__ __forceinline__ static double* U(const F& f, int l) { return f.v[l]; }
+  __device__ __forceinline__ static const double* A(const F&, int) { return nullptr; }
+  __device__ __forceinline__ static const double* B(const F& f, int l) { return f.S[l]; }
+  __device__ __forceinline__ static const double* D(const F& f, int l) { return f.dens[l]; }
+  __device__ __forceinline__ double update(double h2, const SmallCell<T>& c, double old,
+                                           double sum) const {
+    return direct_update<M, double>(C, h2, old, sum, c.d, c.b);
+  }
+  __device__ __forceinline__ double resid(double h2, const SmallCell<T>& c, double u,
+                                          double sum) const {
+    return direct_resid<M, double>(C, h2, u, sum, c.d, c.b);
+  }
+  __device__ __forceinline__ double diag(double h2, const SmallCell<T>& c, double u) const {
+    return direct_diag<M, double>(C, h2, u, c.d) + 6.0 / h2;
+  }
+  __device__ __forceinline__ static double mu(double D, double J) { return -D / J; }
+};
+template <typename TT>
+struct SmallLin {
+  typedef TT T;
+  typedef FusedLin<T> F;
+  static constexpr bool kA = true, kD = false, kR = false, kOld = false, kMean = true;
+  __device__ __forceinline__ static T par(const F& f, int l) { return f.kh2[l]; }
+  __device__ __forceinline__ static T* U(const F& f, int l) { return f.e[l]; }
+  __device__ __forceinline__ static const T* A(const F& f, int l) { return f.dg[l]; }
+  __device__ __forceinline__ static const T* B(const F& f, int l) { return f.r[l]; }
+  __device__ __forceinline__ static const T* D(const F&, int) { return nullptr; }
+  __device__ __forceinline__ T update(T kh2, const SmallCell<T>& c, T, T sum) const {
+    return (c.b + kh2 * sum) / (T(6) * kh2 + c.a);
+  }
+  __device__ __forceinline__ T resid(T kh2, const SmallCell<T>& c, T u, T sum) const {
+    return c.b - (kh2 * (T(6) * u - sum) + c.a * u);
+  }
+  __device__ __forceinline__ double diag(T, const SmallCell<T>& c, T) const { return double(c.a); }
+  __device__ __forceinline__ static T mu(double D, double J) { return T(D / J); }
+};
+
+// LDS elements: per level U, [A], B, [D] and, below the first, [R]; then one
+// scratch array of the first level's size (cell residuals, or the coarse
+// correction in natural order)
+template <class P>
+__host__ __device__ constexpr int small_arrays(bool first) {
+  return 2 + (P::kA ? 1 : 0) + (P::kD ? 1 : 0) + (P::kR && !first ? 1 : 0);
+}
+template <class P>
+__host__ inline size_t small_lds_bytes(const Lev* L, int nlev) {
+  int64_t t = 2 * L[0].half;
+  for (int l = 0; l < nlev; ++l) t += small_arrays<P>(l == 0) * 2 * L[l].half;
+  return (size_t)t * sizeof(typename P::T);
+}
+
+template <class P>
+__device__ __forceinline__ void small_cycle(const typename P::F& F, const FusedProg& G, const P& pol,
+                                            typename P::T* lds, double* sh) {
+  typedef typename P::T T;
+  const int tid = threadIdx.x, nt = kFusedThreads;
+  auto cells = [&](int l) { return 2 * (int)F.L[l].half; };
+  auto base = [&](int l) {
+    int o = 0;
+    for (int q = 0; q < l; ++q) o += small_arrays<P>(q == 0) * cells(q);
+    return lds + o;
+  };
+  constexpr int iB = P::kA ? 2 : 1, iD = iB + 1, iR = iB + (P::kD ? 2 : 1);
+  T* const Z = base(F.nlev);
+  {
+    T* b = base(0);
+    const int m = cells(0);
+    for (int g = tid; g < m; g += nt) {
+      b[g] = P::U(F, 0)[g];
+      b[iB * m + g] = P::B(F, 0)[g];
+    }
+    // the correction form's coarser X are restricted by the program
+    for (int l = 0; l < F.nlev; ++l) {
+      T* bl = base(l);
+      const int ml = cells(l);
+      for (int g = tid; g < ml; g += nt) {
+        if (P::kA && (l == 0 || !P::kR)) bl[ml + g] = P::A(F, l)[g];
+        if (P::kD) bl[iD * ml + g] = P::D(F, l)[g];
+      }
+    }
+  }
+  __syncthreads();
+  for (int o = 0; o < G.nops; ++o) {
+    const Op op = G.op[o];
+    const int l = op.lev, m = cells(l);
+    const Lev L = F.L[l];
+    const int half = (int)L.half;
+    const T par = P::par(F, l);
+    T* const b = base(l);
+    auto cell = [&](const T* bl, int ml, int g) {
+      SmallCell<T> c;
+      c.a = P::kA ? bl[ml + g] : T(0);
+      c.b = bl[iB * ml + g];
+      c.d = P::kD ? bl[iD * ml + g] : T(0);
+      return c;
+    };
+    // After every fourth sweep of the coarsest level: v = {sum d^2, sum d, sum
+    // of the diagonals} of this thread's cells, summed over the workgroup (one:
+    // over the wave).  The sums end in the same registers of every thread.
+    constexpr int nv = P::kMean ? 3 : 1;
+    auto total = [&](double* v, bool one) {
+#pragma unroll
+      for (int i = 0; i < nv; ++i) v[i] = wave_sum(v[i]);
+      if (one) {
+#pragma unroll
+        for (int i = 0; i < nv; ++i) v[i] = __shfl(v[i], 0, 64);
+        return;
+      }
+      // sh is written again only after the barriers of the next sweeps
+      if ((tid & 63) == 0) {
+#pragma unroll
+        for (int i = 0; i < nv; ++i) sh[16 * i + (tid >> 6)] = v[i];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < nv; ++i) {
+        v[i] = 0.0;
+        for (int w = 0; w < kFusedThreads / 64; ++w) v[i] += sh[16 * i + w];
+      }
+    };
+    if (op.kind == OP_COARSEST && half <= kSmallSplit) {
+      // one cell per thread, the two colours on different threads
+      const int S = half <= 32 ? 32 : (half <= 128 ? 128 : kSmallSplit);
+      const bool one = S == 32;
+      if (!one || tid < 64) {
+        const int col = tid >= S ? 1 : 0;
+        SmallPos p = small_pos(L, tid - col * S);
+        if (tid >= 2 * S) p.ok = false;
+        p.xe[0] = p.xe[col];
+        const SmallCell<T> c = cell(b, m, col * half + p.g);
+        T* own = b + col * half + p.g;
+        const T* oth = b + (1 - col) * half;
+        auto sync = [&] {
+          if (one) wave_lds_fence();
+          else __syncthreads();
+        };
+        double r0 = -1.0;
+        for (int it = 0; it < G.coarse_sweeps; ++it) {
+#pragma unroll 1
+          for (int k = 0; k < 2; ++k) {
+            if (p.ok && k == col)
+              *own = pol.update(par, c, P::kOld ? *own : T(0), small_sum<T>(p, oth, 0));
+            sync();
+          }
+          if ((it & 3) != 3 && it + 1 < G.coarse_sweeps) continue;
+          double v[3] = {0.0, 0.0, 0.0};
+          if (p.ok) {
+            const T u = *own;
+            v[1] = double(pol.resid(par, c, u, small_sum<T>(p, oth, 0)));
+            v[0] = v[1] * v[1];
+            if (P::kMean) v[2] = pol.diag(par, c, u);
+          }
+          total(v, one);
+          if (P::kMean && v[2] != 0.0) {  // Newton step on the uniform mode
+            if (p.ok) *own += P::mu(v[1], v[2]);
+            sync();
+          }
+          if (r0 < 0.0) r0 = v[0];
+          if (v[0] <= 1e-16 * r0 || v[0] == 0.0) break;
+        }
+      }
+      __syncthreads();
+    } else if (op.kind == OP_SMOOTH || op.kind == OP_COARSEST) {
+      const int sweeps = op.kind == OP_COARSEST ? G.coarse_sweeps : op.count;
+      SmallPos p[kSmallQ];
+#pragma unroll
+      for (int q = 0; q < kSmallQ; ++q) p[q] = small_pos(L, tid + q * nt);
+      double r0 = -1.0;
+      for (int it = 0; it < sweeps; ++it) {
+#pragma unroll 1
+        for (int col = 0; col < 2; ++col) {
+          T* own = b + col * half;
+          const T* oth = b + (1 - col) * half;
+#pragma unroll
+          for (int q = 0; q < kSmallQ; ++q)
+            if (p[q].ok) {
+              const T old = P::kOld ? own[p[q].g] : T(0);
+              own[p[q].g] = pol.update(par, cell(b, m, col * half + p[q].g), old,
+                                       small_sum<T>(p[q], oth, col));
+            }
+          __syncthreads();
+        }
+        if (op.kind == OP_SMOOTH || ((it & 3) != 3 && it + 1 < sweeps)) continue;
+        double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll 1
+        for (int col = 0; col < 2; ++col)
+#pragma unroll
+          for (int q = 0; q < kSmallQ; ++q)
+            if (p[q].ok) {
+              const SmallCell<T> c = cell(b, m, col * half + p[q].g);
+              const T u = b[col * half + p[q].g];
+              const double d =
+                  double(pol.resid(par, c, u, small_sum<T>(p[q], b + (1 - col) * half, col)));
+              v[0] += d * d;
+              if (P::kMean) {
+                v[1] += d;
+                v[2] += pol.diag(par, c, u);
+              }
+            }
+        total(v, false);
+        if (P::kMean && v[2] != 0.0) {
+          const T mu = P::mu(v[1], v[2]);
+#pragma unroll
+          for (int q = 0; q < kSmallQ; ++q)
+            if (p[q].ok) {
+              b[p[q].g] += mu;
+              b[half + p[q].g] += mu;
+            }
+          __syncthreads();
+        }
+        if (r0 < 0.0) r0 = v[0];
+        if (v[0] <= 1e-16 * r0 || v[0] == 0.0) break;
+      }
+    } else if (op.kind == OP_DOWN) {
+      const Lev Lc = F.L[l + 1];
+      T* const bc = base(l + 1);
+      const int mc = cells(l + 1), nc = Lc.n;
+#pragma unroll 1
+      for (int q = 0; q < kSmallQ; ++q) {
+        const SmallPos p = small_pos(L, tid + q * nt);
+        if (!p.ok) continue;
+#pragma unroll 1
+        for (int col = 0; col < 2; ++col)
+          Z[col * half + p.g] = pol.resid(par, cell(b, m, col * half + p.g), b[col * half + p.g],
+                                          small_sum<T>(p, b + (1 - col) * half, col));
+      }
+      __syncthreads();
+      if (tid < mc) {
+        int I, J, K;
+        dec_nat(tid, Lc, I, J, K);
+        T su = T(0), sd = T(0), sa = T(0);
+#pragma unroll
+        for (int d = 0; d < 2; ++d)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int r = ((2 * K + d) * L.n + 2 * J + e) * nc + I;
+#pragma unroll
+            for (int col = 0; col < 2; ++col) {
+              su += b[col * half + r];
+              sd += Z[col * half + r];
+              if (P::kA && P::kR) sa += b[m + col * half + r];
+            }
+          }
+        const int pc = (int)pk_of(Lc, I, J, K);
+        if (P::kR) {
+          bc[pc] = su * T(0.125);
+          bc[iR * mc + pc] = su * T(0.125);
+          if (P::kA) bc[mc + pc] = sa * T(0.125);
+        } else {
+          bc[pc] = T(0);
+        }
+        bc[iB * mc + pc] = sd * T(0.125);
+      }
+      __syncthreads();
+      if (P::kR) {  // coarse source: L^H(R u) - R d
+        const int hc = (int)Lc.half;
+        const SmallPos p = small_pos(Lc, tid < hc ? tid : tid - hc);
+        const int col = tid < hc ? 0 : 1;
+        if (tid < mc) {
+          const T* Rc = bc + iR * mc;
+          const int g = col * hc + p.g;
+          SmallCell<T> c = cell(bc, mc, g);
+          const T rd = c.b;
+          c.b = T(0);
+          bc[iB * mc + g] =
+              pol.resid(P::par(F, l + 1), c, Rc[g],
+                        (col ? small_sum<T>(p, Rc, 1) : small_sum<T>(p, Rc + hc, 0))) -
+              rd;
+        }
+        __syncthreads();
+      }
+    } else {  // OP_UP: u += P (u_H - R u)
+      const Lev Lc = F.L[l + 1];
+      const T* bc = base(l + 1);
+      const int mc = cells(l + 1), nc = Lc.n;
+      if (tid < mc) {
+        int I, J, K;
+        dec_nat(tid, Lc, I, J, K);
+        const int pc = (int)pk_of(Lc, I, J, K);
+        Z[tid] = P::kR ? bc[pc] - bc[iR * mc + pc] : bc[pc];
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (int q = 0; q < kSmallQ; ++q) {
+        const SmallPos p = small_pos(L, tid + q * nt);
+        if (!p.ok) continue;
+        const int J = p.j >> 1, K = p.k >> 1;
+        const int J1 = (p.j & 1) ? (J + 1 == nc ? 0 : J + 1) : (J == 0 ? nc - 1 : J - 1);
+        const int K1 = (p.k & 1) ? (K + 1 == nc ? 0 : K + 1) : (K == 0 ? nc - 1 : K - 1);
+        const int Im = p.ih == 0 ? nc - 1 : p.ih - 1, Ip = p.ih + 1 == nc ? 0 : p.ih + 1;
+        const int row[2][2] = {{(K * nc + J) * nc, (K1 * nc + J) * nc},
+                               {(K * nc + J1) * nc, (K1 * nc + J1) * nc}};
+        T z0[2][2];  // the nearer column, common to both colours
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int d = 0; d < 2; ++d) z0[e][d] = Z[row[e][d] + p.ih];
+#pragma unroll
+        for (int col = 0; col < 2; ++col) {
+          const int I1 = (p.s0 ^ col) ? Ip : Im;
+          T acc = T(0);
+#pragma unroll
+          for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+              for (int d = 0; d < 2; ++d) {
+                const T w = T((a ? 1 : 3) * (e ? 1 : 3) * (d ? 1 : 3)) * T(1.0 / 64.0);
+                acc += w * (a ? Z[row[e][d] + I1] : z0[e][d]);
+              }
+          b[col * half + p.g] += acc;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  for (int g = tid; g < cells(0); g += nt) P::U(F, 0)[g] = lds[g];
+}
+template <int M, int N>
+__global__ __launch_bounds__(kFusedThreads) void k_small_direct(FusedDirect<double, double> F,
+                                                                FusedProg G, Consts C) {
+  extern __shared__ __align__(16) unsigned char small_lds[];
+  __shared__ double sh[48];
+  small_cycle(F, G, SmallDirect<M>{small_consts<M, N>(C)}, reinterpret_cast<double*>(small_lds), sh);
+}
+template <int M, int N>
+__global__ __launch_bounds__(kFusedThreads) void k_small_corr(FusedCorr F, FusedProg G, Consts C) {
+  extern __shared__ __align__(16) unsigned char small_lds[];
+  __shared__ double sh[48];
+  small_cycle(F, G, SmallCorr<M>{small_consts<M, N>(C)}, reinterpret_cast<float*>(small_lds), sh);
+}
+template <typename T>
+__global__ __launch_bounds__(kFusedThreads) void k_small_lin(FusedLin<T> F, FusedProg G) {
+  extern __shared__ __align__(16) unsigned char small_lds[];
+  __shared__ double sh[48];
+  small_cycle(F, G, SmallLin<T>{}, reinterpret_cast<T*>(small_lds), sh);
 }
 
 }  // namespace mgg

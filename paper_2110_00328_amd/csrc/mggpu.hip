@@ -765,6 +765,14 @@ int make_prog(mg_ctx* ctx, int l, const mg_solver_opts* o, int type, FusedProg* 
   return MG_OK;
 }
 
+// Calls fn with the f(R) exponent as a compile-time constant: 1, or -1 for
+// any (the kernel then takes it from C).
+template <typename Fn>
+void launch_small(const Consts& C, Fn&& fn) {
+  if (C.model == FR && C.fr_n == 1) fn(std::integral_constant<int, 1>{});
+  else fn(std::integral_constant<int, -1>{});
+}
+
 // ---------------------------------------------------------------------------
 // FP64 direct multigrid
 // ---------------------------------------------------------------------------
@@ -815,7 +823,13 @@ int cycle64(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
     }
     FusedProg P;
     ACHK(make_prog(ctx, l, o, type, &P));
-    k_fused_direct<M, double, double><<<1, kFusedThreads, 0, ctx->stream>>>(F, P, C);
+    if (F.L[0].n <= kSmallN)
+      launch_small(C, [&](auto N) {
+        k_small_direct<M, N><<<1, kFusedThreads, small_lds_bytes<SmallDirect<M>>(F.L, F.nlev),
+                               ctx->stream>>>(F, P, C);
+      });
+    else
+      k_fused_direct<M, double, double><<<1, kFusedThreads, 0, ctx->stream>>>(F, P, C);
     LAUNCHCHK();
     return MG_OK;
   }
@@ -1093,7 +1107,13 @@ int cycle32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
     }
     FusedProg P;
     ACHK(make_prog(ctx, l, o, type, &P, rx ? 1 : 0));
-    k_fused_corr<M><<<1, kFusedThreads, 0, ctx->stream>>>(F, P, C);
+    if (F.L[0].n <= kSmallN)
+      launch_small(C, [&](auto N) {
+        k_small_corr<M, N><<<1, kFusedThreads, small_lds_bytes<SmallCorr<M>>(F.L, F.nlev),
+                             ctx->stream>>>(F, P, C);
+      });
+    else
+      k_fused_corr<M><<<1, kFusedThreads, 0, ctx->stream>>>(F, P, C);
     LAUNCHCHK();
     return MG_OK;
   }
@@ -1498,7 +1518,11 @@ int lin_cycle(mg_ctx* ctx, WorkLin<T>& W, double kap, const mg_solver_opts* o, i
     }
     FusedProg P;
     ACHK(make_prog(ctx, l, o, type, &P));
-    k_fused_lin<T><<<1, kFusedThreads, 0, ctx->stream>>>(F, P);
+    if (F.L[0].n <= kSmallN)
+      k_small_lin<T><<<1, kFusedThreads, small_lds_bytes<SmallLin<T>>(F.L, F.nlev),
+                       ctx->stream>>>(F, P);
+    else
+      k_fused_lin<T><<<1, kFusedThreads, 0, ctx->stream>>>(F, P);
     LAUNCHCHK();
     return MG_OK;
   }
@@ -3804,7 +3828,12 @@ int g_cycle(mg_ctx* ctx, hipStream_t st, const GClass& K, const Lev* L,
                                            : default_coarse_sweeps(L[K.nlev - 1].n, K.nlev);
     P.rx = rx ? 1 : 0;
     for (int q = 0; q < ops.n; ++q) P.op[q] = ops.op[q];
-    kg_fused<M><<<K.count, kFusedThreads, 0, st>>>(tab, ctl, it, P);
+    if (L[K.f].n <= kSmallN)
+      // the boxes of a class may differ in the f(R) exponent
+      kg_small<M><<<K.count, kFusedThreads, small_lds_bytes<SmallCorr<M>>(L + K.f, K.nlev - K.f),
+                    st>>>(tab, ctl, it, P);
+    else
+      kg_fused<M><<<K.count, kFusedThreads, 0, st>>>(tab, ctl, it, P);
     LAUNCHCHK();
     return MG_OK;
   }

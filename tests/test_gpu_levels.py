@@ -1,0 +1,88 @@
+"""Kernel forms of single levels against the FP64 oracle, at the grid sizes
+where their tilings and branches end.
+
+Tolerances as for the other parity tests: both sides are converged far below
+the target, so FP64 solves agree to 1e-8 and FP32-refined ones to 1e-6
+(relative to the deviation from the background), adjoints to 1e-8 and 1e-5.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2110_00328_amd import api
+
+pytestmark = pytest.mark.gpu
+
+CH = oracle.C_OVER_H0
+DEV = torch.device("cuda:0")
+KIND = {"fr": oracle.FR, "sym": oracle.SYM, "cq": oracle.CQ}
+
+
+def inputs(model, n, seed, sig=1.0, **kw):
+    """oracle params, ABI params, density contrast"""
+    if model == "sym":
+        kw = dict(a=1.0, a_star=0.5, xi=2.0 / CH, beta_star=1.0, **kw)
+    elif model == "fr":
+        kw = dict(dict(fr0=1e-5), **kw)
+    g = np.random.default_rng(seed).standard_normal((n, n, n))
+    d = np.exp(sig * g - 0.5 * sig * sig) - 1
+    box = float(n)
+    return (oracle.params(KIND[model], n, box, **kw), api.model_params(box, **kw),
+            (d - d.mean()).astype(np.float32))
+
+
+def deviation(model, x, P):
+    x = np.asarray(x, dtype=np.float64)
+    if model == "cq":  # the uniform mode is nearly a null mode
+        return x - x.mean()
+    return x - (-1.0 if model == "fr" else 1.0) * oracle.background(P)
+
+
+def rel_err(model, x, ref, P):
+    a, b = deviation(model, x, P), deviation(model, ref, P)
+    return np.linalg.norm(a - b) / np.linalg.norm(b)
+
+
+def solve_and_adjoint_match(model, n, prec, cycle="V", seed=71, **kw):
+    P, prm, delta = inputs(model, n, seed, **kw)
+    d64 = delta.astype(np.float64)
+    ref, _, _, _ = oracle.solve(P, d64, tol=1e-12)
+    mg = api.Context(n, device=DEV)
+    dt = torch.from_numpy(delta).to(DEV)
+    o = api.solver_opts(precision=prec, cycle=cycle, max_cycles=64)
+    print("solve and adjoint", model, n, prec, cycle, kw, flush=True)
+    field, st = mg.solve(model, prm, dt, tol=1e-11 if prec == "fp64" else 1e-9, opts=o)
+    err = rel_err(model, field.cpu().numpy(), -ref if model == "fr" else ref, P)
+    # adjoint at the oracle's field, right-hand side without a uniform mode
+    gv = np.random.default_rng(seed + 1).standard_normal((n, n, n))
+    gv -= gv.mean()
+    gref, _, _ = oracle.adjoint(P, d64, ref, gv, tol=1e-12, solver="cg")
+    sgn = -1.0 if model == "fr" else 1.0
+    gd, sa = mg.solve_adjoint(model, prm, dt, torch.from_numpy(sgn * ref).to(DEV),
+                              torch.from_numpy(sgn * gv).to(DEV),
+                              tol=1e-11 if prec == "fp64" else 1e-9, opts=o)
+    aerr = np.linalg.norm(gd.cpu().numpy() - gref) / np.linalg.norm(gref)
+    mg.close()
+    print(f"  cycles {st.vcycles} / {sa.vcycles}, field {err:.2e}, adjoint {aerr:.2e}", flush=True)
+    assert err < (1e-8 if prec == "fp64" else 1e-6)
+    assert aerr < (1e-8 if prec == "fp64" else 1e-5)
+
+
+# 8: one cell per thread on the coarsest 4^3; 20 -> 10 and 24 -> 12 -> 6: the
+# colours on different waves; 28 -> 14: a coarsest level of more cells than
+# threads; 32 -> 16: two positions per thread
+# (the oracle solves a coarsest 10^3 of coupled quintessence as one dense
+# system, which takes minutes)
+@pytest.mark.parametrize("model,n", [("fr", 8), ("fr", 20), ("fr", 24), ("fr", 28), ("fr", 32),
+                                     ("sym", 20), ("sym", 28), ("sym", 32),
+                                     ("cq", 16), ("cq", 24), ("cq", 32)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_small_levels_match_oracle(model, prec, n):
+    solve_and_adjoint_match(model, n, prec)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_small_levels_second_visits_and_other_exponents(prec):
+    solve_and_adjoint_match("sym", 32, prec, cycle="W")
+    solve_and_adjoint_match("fr", 32, prec, cycle="F", fr_n=2)
