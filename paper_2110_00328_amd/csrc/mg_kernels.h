@@ -337,70 +337,36 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
   }
   return v;
 }
-// dst = 16-bit (src * enc), four cells per thread (m % 4 == 0)
-__global__ __launch_bounds__(kBlock) void k_to_h16(int64_t m4, const float* __restrict__ src,
-                                                   h16* __restrict__ dst, float enc) {
-  const int64_t g = gid();
-  if (g >= m4) return;
-  float v[4];
-  ld4s<float>(src + 4 * g, 1.0f, v);
-  st4s<h16>(dst + 4 * g, v, enc);
-}
-// block maxima of |x| over m floats
-// block partial maxima of |x| (exact in float), four values per load over
-// a grid-stride loop of kAbsmaxBlocks blocks; x 16-byte aligned
-constexpr int kAbsmaxBlocks = 2048;
-__global__ __launch_bounds__(kBlock) void k_absmax_f32(int64_t m, const float* __restrict__ x,
-                                                       double* __restrict__ part) {
+// Reductions of block partials: up to kRedItems sums or maxima (of values >=
+// 0) per launch, one block column (blockIdx.y) each.  Block b of a column takes
+// the contiguous chunk [b chunk, (b+1) chunk) and writes dst[b]: with one
+// block the result itself, straight into pinned host memory where the caller
+// gives that, so a solve's residual norms reach the host with one launch and
+// no copy.
+constexpr int kRedItems = 3;
+constexpr int kRedBlocks = 256;  // blocks of a first stage
+struct RedItem {
+  const double* src;
+  double* dst;
+  int64_t m;
+  int is_max;
+};
+struct RedItems {
+  RedItem it[kRedItems];
+};
+__global__ __launch_bounds__(1024) void k_reduce(RedItems R) {
   __shared__ double sh[32];
-  const int64_t m4 = m >> 2;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  float v = 0.0f;
-  for (int64_t q = gid(); q < m4; q += stride) {
-    const float4 a = reinterpret_cast<const float4*>(x)[q];
-    v = fmaxf(v, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
-  }
-  for (int64_t q = 4 * m4 + gid(); q < m; q += stride) v = fmaxf(v, fabsf(x[q]));
-  const double t = block_max(double(v), sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = t;
-}
-// Maxima of fixed chunks of m partial maxima, one block per chunk
-__global__ void k_max_chunks(const double* __restrict__ part, int64_t m, int64_t chunk,
-                             double* __restrict__ out) {
-  __shared__ double sh[32];
+  const RedItem I = R.it[blockIdx.y];
+  const int64_t chunk = (I.m + gridDim.x - 1) / gridDim.x;
   const int64_t lo = (int64_t)blockIdx.x * chunk;
-  const int64_t hi = lo + chunk < m ? lo + chunk : m;
+  const int64_t hi = lo + chunk < I.m ? lo + chunk : I.m;
   double v = 0.0;
-  for (int64_t q = lo + threadIdx.x; q < hi; q += blockDim.x) v = fmax(v, part[q]);
-  v = block_max(v, sh);
-  if (threadIdx.x == 0) out[blockIdx.x] = v;
-}
-// Maximum of m partial maxima (one block)
-__global__ void k_max_partials(const double* __restrict__ part, int64_t m, double* out) {
-  __shared__ double sh[32];
-  double v = 0.0;
-  for (int64_t q = threadIdx.x; q < m; q += blockDim.x) v = fmax(v, part[q]);
-  v = block_max(v, sh);
-  if (threadIdx.x == 0) *out = v;
-}
-
-// stage 1: block b sums the contiguous chunk [b*chunk, (b+1)*chunk)
-__global__ void k_sum_chunks(const double* __restrict__ part, int64_t m, int64_t chunk,
-                             double* __restrict__ out) {
-  __shared__ double sh[32];
-  int64_t lo = (int64_t)blockIdx.x * chunk;
-  int64_t hi = lo + chunk < m ? lo + chunk : m;
-  double s = 0.0;
-  for (int64_t q = lo + threadIdx.x; q < hi; q += blockDim.x) s += part[q];
-  double t = block_sum(s, sh);
-  if (threadIdx.x == 0) out[blockIdx.x] = t;
-}
-__global__ void k_sum_partials(const double* __restrict__ part, int64_t m, double* out, int slot) {
-  __shared__ double sh[32];
-  double s = 0.0;
-  for (int64_t q = threadIdx.x; q < m; q += blockDim.x) s += part[q];
-  double t = block_sum(s, sh);
-  if (threadIdx.x == 0) out[slot] = t;
+  if (I.is_max)
+    for (int64_t q = lo + threadIdx.x; q < hi; q += blockDim.x) v = fmax(v, I.src[q]);
+  else
+    for (int64_t q = lo + threadIdx.x; q < hi; q += blockDim.x) v += I.src[q];
+  v = I.is_max ? block_max(v, sh) : block_sum(v, sh);
+  if (threadIdx.x == 0) I.dst[blockIdx.x] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -946,7 +912,13 @@ constexpr int kVOuter = 4;  // cells per colour per thread in the outer kernels 
 // from L1/L2.  Consecutive blocks take neighbouring chunks of the same planes.
 // Same per-cell arithmetic and neighbour summation order as the kernels above.
 // ---------------------------------------------------------------------------
-constexpr int kMarchKT = 16;
+constexpr int kMarchKT = 16;  // planes per block on grids that fill the chip
+// fewest workgroups of a marching FP64 or force launch: below, the planes per
+// block are halved (each block then reads its two outside planes for fewer of
+// its own, which costs L2 traffic only, while a sparse grid leaves compute
+// units idle).  FP64 outer step: 7 us at 32^3 (2 workgroups of 16 planes: 50),
+// 79 at 192^3 for CQ (123), 83 at 256^3 for the symmetron (102).
+constexpr unsigned kMarchMinBlocks = 1024;
 
 struct MarchPos {
   int j, jm, jp, ih0, k0, k1;
@@ -975,6 +947,12 @@ __host__ __device__ inline unsigned march_blocks(const Lev& L, int kt, int V) {
   unsigned ngrp = (unsigned)((uint64_t)L.n * (uint64_t)L.nh / (uint64_t)V);
   unsigned nchunk = (ngrp + kBlock - 1) / kBlock;
   return nchunk * (unsigned)((L.n + kt - 1) / kt);
+}
+// planes per block of a march with nblk1 blocks per slab of planes
+__host__ inline int march_depth(int n, unsigned nblk1) {
+  int kt = kMarchKT;
+  while (kt > 1 && nblk1 * (unsigned)((n + kt - 1) / kt) < kMarchMinBlocks) kt /= 2;
+  return kt;
 }
 // The same half-sweep marching in z: a thread owns 4 packed cells of its
 // colour in row j and walks kt planes, keeping the other colour's rows
@@ -1969,6 +1947,37 @@ __device__ __forceinline__ void ld_coarse4(const Lev& Lc, const T* __restrict__ 
   v[1] = od.x;
   v[3] = od.y;
 }
+// Restriction of a level-0 coefficient (op_restrict) together with its 16-bit
+// copy dst = h16(f enc): one pass over f instead of two (146 us at 512^3, 6 TB/s,
+// against 134 + 129).  4 coarse cells per thread (nc % 4 == 0).
+__global__ __launch_bounds__(kBlock) void k_restrict_h16(Lev Lf, Lev Lc,
+                                                         const float* __restrict__ f,
+                                                         float* __restrict__ c,
+                                                         h16* __restrict__ dst, float enc) {
+  const uint32_t g4 = (uint32_t)gid();
+  if (g4 >= (uint32_t)(2 * Lc.half / 4)) return;
+  int I0, J, K;
+  dec_nat(g4 * 4, Lc, I0, J, K);
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const uint32_t row = prow(Lf, 2 * J + b, 2 * K + d) + (uint32_t)I0;
+      float v0[4], v1[4];
+      ld4s<float>(f + row, 1.0f, v0);
+      ld4s<float>(f + Lf.half + row, 1.0f, v1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] += double(v0[q]) + double(v1[q]);
+      st4s<h16>(dst + row, v0, enc);
+      st4s<h16>(dst + Lf.half + row, v1, enc);
+    }
+  float o[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) o[q] = float(s[q] * 0.125);
+  st_coarse4<float>(Lc, c, I0, J, K, o);
+}
+
 struct RRPos {
   int I0, J, Jm2, Jp2, K0, K1;  // Jm2 = fine row 2J-1, Jp2 = fine row 2J+2 (periodic)
   bool ok;

@@ -149,8 +149,7 @@ struct mg_ctx {
   double* part2 = nullptr;
   double* part3 = nullptr;     // second set of block partials (same capacity as part)
   int64_t part_cap = 0;
-  double* scal = nullptr;      // device scalars
-  double* hscal = nullptr;     // pinned host mirror
+  double* hscal = nullptr;     // pinned host scalars, written by k_reduce
   int64_t* cic = nullptr;      // CIC fixed-point accumulator (direct path)
   uint2* cic_rec = nullptr;     // binned CIC: run records, one region per count block
   uint32_t* cic_nrec = nullptr;  // records per region
@@ -634,61 +633,58 @@ int plan_cycles(int fixed, double rel, double rel_prev, int k_prev, double tol, 
 // ---------------------------------------------------------------------------
 // reductions to the host
 // ---------------------------------------------------------------------------
-// deterministic: fixed chunks summed by up to 256 blocks, then one block
-int sum_on_device(mg_ctx* ctx, int64_t nparts, double* dst, const double* src = nullptr) {
-  int64_t nb = (nparts + 2047) / 2048;
-  if (nb > 256) nb = 256;
-  int64_t chunk = (nparts + nb - 1) / nb;
-  k_sum_chunks<<<(unsigned)nb, 256, 0, ctx->stream>>>(src ? src : ctx->part, nparts, chunk,
-                                                      ctx->part2);
-  k_sum_partials<<<1, 256, 0, ctx->stream>>>(ctx->part2, nb, dst, 0);
+// Sums and maxima of partials (RedItem) into their dst, in one launch, or two
+// for more than kRedOne partials; deterministic (fixed chunks, fixed order).
+constexpr int64_t kRedOne = 16384;
+int reduce(mg_ctx* ctx, std::initializer_list<RedItem> items) {
+  RedItems A{}, B{};
+  unsigned k = 0;
+  int64_t most = 0;
+  for (const RedItem& it : items) {
+    A.it[k] = B.it[k] = it;
+    A.it[k].dst = ctx->part2 + k * kRedBlocks;
+    B.it[k].src = A.it[k].dst;
+    B.it[k].m = kRedBlocks;
+    most = std::max(most, it.m);
+    ++k;
+  }
+  if (most <= kRedOne) {
+    k = 0;
+    for (const RedItem& it : items) A.it[k++] = it;
+    k_reduce<<<dim3(1, k), 1024, 0, ctx->stream>>>(A);
+  } else {
+    k_reduce<<<dim3(kRedBlocks, k), 256, 0, ctx->stream>>>(A);
+    k_reduce<<<dim3(1, k), 256, 0, ctx->stream>>>(B);
+  }
   LAUNCHCHK();
   return MG_OK;
 }
 
-// the same for maxima of non-negative partials: src -> *dst on the device
-int max_on_device(mg_ctx* ctx, int64_t nparts, const double* src, double* dst) {
-  int64_t nb = (nparts + 2047) / 2048;
-  if (nb > 256) nb = 256;
-  const int64_t chunk = (nparts + nb - 1) / nb;
-  k_max_chunks<<<(unsigned)nb, 256, 0, ctx->stream>>>(src, nparts, chunk, ctx->part2);
-  k_max_partials<<<1, 256, 0, ctx->stream>>>(ctx->part2, nb, dst);
-  LAUNCHCHK();
+// the same to the host (the last stage writes pinned host memory), one
+// synchronisation: results in ctx->hscal[0..]
+int reduce_to_host(mg_ctx* ctx, std::initializer_list<RedItem> items) {
+  ACHK(reduce(ctx, items));
+  HIPCHK(hipStreamSynchronize(ctx->stream));
   return MG_OK;
 }
 
 int sum_to_host(mg_ctx* ctx, int64_t nparts, double* out, const double* src = nullptr) {
-  ACHK(sum_on_device(ctx, nparts, ctx->scal, src));
-  HIPCHK(hipMemcpyAsync(ctx->hscal, ctx->scal, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-  HIPCHK(hipStreamSynchronize(ctx->stream));
+  ACHK(reduce_to_host(ctx, {RedItem{src ? src : ctx->part, ctx->hscal, nparts, 0}}));
   *out = ctx->hscal[0];
   return MG_OK;
 }
 
-// two sums with one synchronisation: ctx->part -> *a, src_b -> *b
-int sum2_to_host(mg_ctx* ctx, int64_t nparts, double* a, double* b, const double* src_b) {
-  ACHK(sum_on_device(ctx, nparts, ctx->scal));
-  ACHK(sum_on_device(ctx, nparts, ctx->scal + 1, src_b));
-  HIPCHK(hipMemcpyAsync(ctx->hscal, ctx->scal, 2 * sizeof(double), hipMemcpyDeviceToHost,
-                        ctx->stream));
-  HIPCHK(hipStreamSynchronize(ctx->stream));
-  *a = ctx->hscal[0];
-  *b = ctx->hscal[1];
-  return MG_OK;
-}
-
-// Reductions of one refined outer pass with one synchronisation: sum d^2
-// (ctx->part) -> *s; with bg, sum (bg_coef delta)^2 (ctx->part3) -> *sb; with
-// mx_on, max |d| (ctx->part4) -> *mx.
+// Reductions of one refined outer pass: sum d^2 (ctx->part) -> *s; with bg,
+// sum (bg_coef delta)^2 (ctx->part3) -> *sb; with mx_on, max |d| (ctx->part4)
+// -> *mx.
 int outer_sums(mg_ctx* ctx, int64_t nparts, bool bg, bool mx_on, double* s, double* sb,
                double* mx) {
-  ACHK(sum_on_device(ctx, nparts, ctx->scal));
-  if (bg) ACHK(sum_on_device(ctx, nparts, ctx->scal + 1, ctx->part3));
-  if (mx_on) ACHK(max_on_device(ctx, nparts, ctx->part4, ctx->scal + 2));
-  LAUNCHCHK();
-  HIPCHK(hipMemcpyAsync(ctx->hscal, ctx->scal, 3 * sizeof(double), hipMemcpyDeviceToHost,
-                        ctx->stream));
-  HIPCHK(hipStreamSynchronize(ctx->stream));
+  const RedItem d{ctx->part, ctx->hscal, nparts, 0}, b{ctx->part3, ctx->hscal + 1, nparts, 0},
+      x{ctx->part4, ctx->hscal + 2, nparts, 1};
+  if (bg && mx_on) ACHK(reduce_to_host(ctx, {d, b, x}));
+  else if (bg) ACHK(reduce_to_host(ctx, {d, b}));
+  else if (mx_on) ACHK(reduce_to_host(ctx, {d, x}));
+  else ACHK(reduce_to_host(ctx, {d}));
   *s = ctx->hscal[0];
   if (bg) *sb = ctx->hscal[1];
   if (mx_on) *mx = ctx->hscal[2];
@@ -1265,7 +1261,8 @@ int solve32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const float* 
     double s, sb = 0.0;
     if (fused) {
       // w_new = w + pending, residual at w_new, next correction buffer zeroed
-      nparts = march_blocks(L0, kMarchKT, kVOuter);
+      const int mkt = march_depth(L0.n, march_blocks(L0, L0.n, kVOuter));
+      nparts = march_blocks(L0, mkt, kVOuter);
       double* wn = pending ? W.wbuf[1 - cur] : W.w;
       float* ez = fresh ? nullptr : W.ebuf[pending ? 1 - eb : eb];
       const double* wsrc = (uni && outer <= 1) ? nullptr : W.w;
@@ -1290,7 +1287,7 @@ int solve32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const float* 
           using TR = std::remove_pointer_t<decltype(R)>;
           k_outer_fused_kv<M, TX, TR><<<(unsigned)nparts, kBlock, 0, ctx->stream>>>(
               L0, wsrc, pending, wn, W.dens[0], C, R, X, ez, ctx->part,
-              bgsum ? ctx->part3 : nullptr, kMarchKT, ctx->s0.S, r16 ? ctx->part4 : nullptr);
+              bgsum ? ctx->part3 : nullptr, mkt, ctx->s0.S, r16 ? ctx->part4 : nullptr);
         });
         LAUNCHCHK();
         double mx = 0.0;
@@ -1377,17 +1374,19 @@ int solve32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const float* 
 // The whole adjoint set-up in one pass over the natural cells: the solved
 // variable v = sgn field, the Jacobian diagonal dg (FP64, and FP32 when dg32
 // is given), the right-hand side b = bsign grad, packed; v itself only when
-// the final step needs it (v_out non-null); block partials of b^2.
+// the final step needs it (v_out non-null); block partials of b^2 and, when
+// part_max is given, of max |dg|.
 template <int M>
 __global__ __launch_bounds__(kBlock) void k_lin_setup_nat(Lev L, const double* __restrict__ field,
                                                           const float* __restrict__ delta,
                                                           const double* __restrict__ grad,
                                                           double sgn, double bsign, Consts C,
                                                           double* v_out, double* dg, float* dg32,
-                                                          double* b, double* part) {
+                                                          double* b, double* part,
+                                                          double* part_max) {
   __shared__ double sh[32];
   int64_t g = gid();
-  double bb = 0.0;
+  double bb = 0.0, dm = 0.0;
   if (g < 2 * L.half) {
     int i, j, k;
     dec_nat(g, L, i, j, k);
@@ -1396,6 +1395,7 @@ __global__ __launch_bounds__(kBlock) void k_lin_setup_nat(Lev L, const double* _
     const double d = lin_dg<M>(C, v, double(delta[g]));
     dg[pk] = d;
     if (dg32) dg32[pk] = float(d);
+    dm = fabs(double(float(d)));
     if (v_out) v_out[pk] = v;
     const double bv = bsign * grad[g];
     b[pk] = bv;
@@ -1403,6 +1403,10 @@ __global__ __launch_bounds__(kBlock) void k_lin_setup_nat(Lev L, const double* _
   }
   double t = block_sum(bb, sh);
   if (threadIdx.x == 0) part[blockIdx.x] = t;
+  if (part_max) {  // uniform over the grid
+    t = block_max(dm, sh);
+    if (threadIdx.x == 0) part_max[blockIdx.x] = t;
+  }
 }
 // The same set-up on 8 natural cells of a row per thread (n % 8 == 0,
 // 16-byte aligned caller arrays): the row's even cells are 4 consecutive
@@ -1413,10 +1417,12 @@ __global__ __launch_bounds__(kBlock) void k_lin_setup_nat8(Lev L, const double* 
                                                            const double* __restrict__ grad,
                                                            double sgn, double bsign, Consts C,
                                                            double* v_out, double* dg, float* dg32,
-                                                           double* b, double* part) {
+                                                           double* b, double* part,
+                                                           double* part_max) {
   __shared__ double sh[32];
   const int64_t g8 = gid();
   double bb = 0.0;
+  float dm = 0.0f;
   if (g8 < 2 * L.half / 8) {
     const uint32_t g = (uint32_t)g8 * 8u;
     int i0, j, k;
@@ -1444,6 +1450,7 @@ __global__ __launch_bounds__(kBlock) void k_lin_setup_nat8(Lev L, const double* 
       bo[q] = bsign * gr[2 * q + 1];
       bb += be[q] * be[q];
       bb += bo[q] * bo[q];
+      dm = fmaxf(dm, fmaxf(fabsf(de32[q]), fabsf(do32[q])));
     }
     stn<double, 4>(dg + pe, de);
     stn<double, 4>(dg + po, dodd);
@@ -1460,6 +1467,10 @@ __global__ __launch_bounds__(kBlock) void k_lin_setup_nat8(Lev L, const double* 
   }
   double t = block_sum(bb, sh);
   if (threadIdx.x == 0) part[blockIdx.x] = t;
+  if (part_max) {  // uniform over the grid
+    t = block_max(double(dm), sh);
+    if (threadIdx.x == 0) part_max[blockIdx.x] = t;
+  }
 }
 template <int M>
 __global__ __launch_bounds__(kBlock) void k_lin_final8(Lev L, const double* v, const double* lam,
@@ -1636,6 +1647,9 @@ int adjoint_impl(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const fl
   A.lam = A.lambuf[cur];
   if (A.have32) A.w32.e[0] = A.w32.ebuf[eb];
   if (A.have64) A.w64.e[0] = A.w64.ebuf[eb];
+  // 16-bit dg and r on level 0 of an FP32 solve (as the forward solve's X and
+  // rho; not for CQ): dg scaled so that its largest value maps to ~2^15
+  const bool f16 = f32 && ctx->fp16 && vec && L0.n % 8 == 0 && M != CQ;
   // v, dg, b in one pass; b = s dL/dv, s = +1 (f(R)) / -1, and
   // dL/dv = sgn_field dL/dfield.  v is kept only where dL/d(delta) needs it.
   const bool nat8 = L0.n % 8 == 0 && al16(field, delta) && al16(grad_field, grad_delta);
@@ -1644,21 +1658,22 @@ int adjoint_impl(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const fl
     k_lin_setup_nat8<M><<<nb_setup, kBlock, 0, ctx->stream>>>(
         L0, field, delta, grad_field, sgn_field, lin_sign(C) * sgn_field, C,
         M == FR ? (double*)nullptr : A.v, A.dg, f32 ? A.w32.dg[0] : (float*)nullptr, A.b,
-        ctx->part);
+        ctx->part, f16 ? ctx->part4 : nullptr);
   else
     k_lin_setup_nat<M><<<nb_setup, kBlock, 0, ctx->stream>>>(
         L0, field, delta, grad_field, sgn_field, lin_sign(C) * sgn_field, C,
         M == FR ? (double*)nullptr : A.v, A.dg, f32 ? A.w32.dg[0] : (float*)nullptr, A.b,
-        ctx->part);
+        ctx->part, f16 ? ctx->part4 : nullptr);
   LAUNCHCHK();
-  double bb;
-  ACHK(sum_to_host(ctx, nb_setup, &bb));
-  bb = sqrt(bb);
+  const RedItem rb{ctx->part, ctx->hscal, (int64_t)nb_setup, 0},
+      rd{ctx->part4, ctx->hscal + 1, (int64_t)nb_setup, 1};
+  if (f16) ACHK(reduce_to_host(ctx, {rb, rd}));
+  else ACHK(reduce_to_host(ctx, {rb}));
+  double bb = sqrt(ctx->hscal[0]);
+  const double dmax = f16 ? ctx->hscal[1] : 0.0;
   if (!(bb > 0.0)) bb = 1.0;
   // lam starts at 0: the fused outer kernels take it as 0 until written
   if (!vec) k_fill<double><<<nblk(m), kBlock, 0, ctx->stream>>>(A.lam, m, 0.0);
-  // 16-bit dg and r on level 0 of an FP32 solve (as the forward solve's X and
-  // rho; not for CQ): dg scaled so that its largest value maps to ~2^15
   struct A0Reset {  // level 0 is FP32 again outside this solve
     mg_ctx* c;
     ~A0Reset() {
@@ -1666,30 +1681,19 @@ int adjoint_impl(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const fl
       c->a0.S = Store{1.0f, 1.0f, 1.0f, 1.0f};
     }
   } a0_reset{ctx};
-  const bool f16 = f32 && ctx->fp16 && vec && L0.n % 8 == 0 && M != CQ;
   if (f32) {
-    for (int l = 0; l + 1 < ctx->nlev; ++l)
-      k_restrict<float, float><<<nblk(cells(ctx->L[l + 1])), kBlock, 0, ctx->stream>>>(
-          ctx->L[l], ctx->L[l + 1], A.w32.dg[l], A.w32.dg[l + 1]);
     if (f16) {
-      // at most nblk(m) <= part_cap partials
-      const unsigned nb = std::min<unsigned>(kAbsmaxBlocks, nblk((m + 3) / 4));
-      k_absmax_f32<<<nb, kBlock, 0, ctx->stream>>>(m, A.w32.dg[0], ctx->part4);
-      ACHK(max_on_device(ctx, nb, ctx->part4, ctx->scal + 2));
-      HIPCHK(hipMemcpyAsync(ctx->hscal + 2, ctx->scal + 2, sizeof(double), hipMemcpyDeviceToHost,
-                            ctx->stream));
-      HIPCHK(hipStreamSynchronize(ctx->stream));
-      const double dmax = ctx->hscal[2];
       const int dexp = dmax > 0.0 && std::isfinite(dmax) ? (int)floor(log2(3.2e4 / dmax)) : 0;
       ctx->a0.on = std::isfinite(dmax) && dexp > -120 && dexp < 120;
       ctx->a0.S.x_enc = float(ldexp(1.0, dexp));
       ctx->a0.S.x_dec = float(ldexp(1.0, -dexp));
-      if (ctx->a0.on) {
-        k_to_h16<<<nblk(m / 4), kBlock, 0, ctx->stream>>>(m / 4, A.w32.dg[0], A.w32.dg16,
-                                                           ctx->a0.S.x_enc);
-        LAUNCHCHK();
-      }
     }
+    if (ctx->a0.on)  // n % 8 == 0: there is a coarser level, of a multiple of 4 cells a side
+      k_restrict_h16<<<nblk(cells(ctx->L[1]) / 4), kBlock, 0, ctx->stream>>>(
+          L0, ctx->L[1], A.w32.dg[0], A.w32.dg[1], A.w32.dg16, ctx->a0.S.x_enc);
+    for (int l = ctx->a0.on ? 1 : 0; l + 1 < ctx->nlev; ++l)
+      k_restrict<float, float><<<nblk(cells(ctx->L[l + 1])), kBlock, 0, ctx->stream>>>(
+          ctx->L[l], ctx->L[l + 1], A.w32.dg[l], A.w32.dg[l + 1]);
   } else {
     for (int l = 0; l + 1 < ctx->nlev; ++l)
       k_restrict<double, double><<<nblk(cells(ctx->L[l + 1])), kBlock, 0, ctx->stream>>>(
@@ -1719,7 +1723,8 @@ int adjoint_impl(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const fl
   const bool fresh = vec && L0.nh % (f32 ? Vec<float>::V : Vec<double>::V) == 0 &&
                      o->nu_pre > 0 && ctx->fused_from > 0;
   for (;;) {
-    int64_t nparts = vec ? march_blocks(L0, kMarchKT, kVOuter) : nblk(m);
+    const int mkt = march_depth(L0.n, march_blocks(L0, L0.n, kVOuter));
+    int64_t nparts = vec ? march_blocks(L0, mkt, kVOuter) : nblk(m);
     double s_pass = -1.0;  // sum r^2 when the 16-bit pass has reduced it already
     if (vec) {
       double* ln = pending ? A.lambuf[1 - cur] : A.lam;
@@ -1737,7 +1742,7 @@ int adjoint_impl(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const fl
           ctx->a0.S.r_dec = float(ldexp(1.0, -rexp));
           k_lin_outer_fused_kv<float, h16><<<(unsigned)nparts, kBlock, 0, ctx->stream>>>(
               L0, lsrc, (const float*)pending, ln, A.dg, A.b, kap, A.w32.r16,
-              fresh ? (float*)nullptr : A.w32.ebuf[ez], ctx->part, shift, psum, kMarchKT,
+              fresh ? (float*)nullptr : A.w32.ebuf[ez], ctx->part, shift, psum, mkt,
               ctx->a0.S, ctx->part4);
           LAUNCHCHK();
           double mx = 0.0, s0 = 0.0, sb0 = 0.0;
@@ -1749,11 +1754,11 @@ int adjoint_impl(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const fl
       } else if (f32)
         k_lin_outer_fused_kv<float><<<(unsigned)nparts, kBlock, 0, ctx->stream>>>(
             L0, lsrc, (const float*)pending, ln, A.dg, A.b, kap, A.w32.r[0],
-            fresh ? (float*)nullptr : A.w32.ebuf[ez], ctx->part, shift, psum, kMarchKT);
+            fresh ? (float*)nullptr : A.w32.ebuf[ez], ctx->part, shift, psum, mkt);
       else
         k_lin_outer_fused_kv<double><<<(unsigned)nparts, kBlock, 0, ctx->stream>>>(
             L0, lsrc, (const double*)pending, ln, A.dg, A.b, kap, A.w64.r[0],
-            fresh ? (double*)nullptr : A.w64.ebuf[ez], ctx->part, shift, psum, kMarchKT);
+            fresh ? (double*)nullptr : A.w64.ebuf[ez], ctx->part, shift, psum, mkt);
       if (pending) {
         cur = 1 - cur;
         eb = 1 - eb;
@@ -1883,7 +1888,7 @@ __global__ __launch_bounds__(kBlock) void k_force(Lev L, const double* __restric
 }
 
 // The same force with a march in z: a thread owns 4 consecutive cells of a
-// row and walks kMarchKT planes, keeping Phi5 of planes k-1, k, k+1 in
+// row and walks kt planes, keeping Phi5 of planes k-1, k, k+1 in
 // registers (the field is read from HBM once); rows j +- 1 and the row's
 // edge cells come from L1/L2.  Requires n % 4 == 0.
 template <bool ADD>
@@ -2722,7 +2727,7 @@ int scratch_base(mg_ctx* ctx, char** out) {
 struct NoallocWork {
   Work32 w32;
   Work64 w64;
-  double *part = nullptr, *part2 = nullptr, *part3 = nullptr, *part4 = nullptr, *scal = nullptr;
+  double *part = nullptr, *part2 = nullptr, *part3 = nullptr, *part4 = nullptr;
 };
 size_t noalloc_layout(const mg_ctx* ctx, char* base, NoallocWork* W) {
   size_t off = 0;
@@ -2732,10 +2737,9 @@ size_t noalloc_layout(const mg_ctx* ctx, char* base, NoallocWork* W) {
     return p;
   };
   W->part = (double*)take(sizeof(double) * (size_t)ctx->part_cap);
-  W->part2 = (double*)take(sizeof(double) * 256);
+  W->part2 = (double*)take(sizeof(double) * kRedItems * kRedBlocks);
   W->part3 = (double*)take(sizeof(double) * (size_t)ctx->part_cap);
   W->part4 = (double*)take(sizeof(double) * (size_t)ctx->part_cap);
-  W->scal = (double*)take(sizeof(double) * 16);
   const size_t m0 = (size_t)cells(ctx->L[0]);
   W->w32.wbuf[0] = (double*)take(8 * m0);
   W->w32.wbuf[1] = (double*)take(8 * m0);
@@ -2769,10 +2773,10 @@ struct NoallocScope {
   Work32 w32;
   Work64 w64;
   bool h32, h64;
-  double *part, *part2, *part3, *part4, *scal;
+  double *part, *part2, *part3, *part4;
   NoallocScope(mg_ctx* x, const NoallocWork& W)
       : c(x), w32(x->w32), w64(x->w64), h32(x->have32), h64(x->have64), part(x->part),
-        part2(x->part2), part3(x->part3), part4(x->part4), scal(x->scal) {
+        part2(x->part2), part3(x->part3), part4(x->part4) {
     c->w32 = W.w32;
     c->w64 = W.w64;
     c->have32 = c->have64 = true;
@@ -2780,7 +2784,6 @@ struct NoallocScope {
     c->part2 = W.part2;
     c->part3 = W.part3;
     c->part4 = W.part4;
-    c->scal = W.scal;
     c->noalloc = true;
   }
   ~NoallocScope() {
@@ -2792,7 +2795,6 @@ struct NoallocScope {
     c->part2 = part2;
     c->part3 = part3;
     c->part4 = part4;
-    c->scal = scal;
     c->noalloc = false;
   }
 };
@@ -2853,10 +2855,9 @@ int mg_ctx_create(mg_ctx** out, int n, void* hip_stream) {
   ctx->fused_from = f;
   ctx->part_cap = nblk((int64_t)n * n * n) + 16;
   int rc = dalloc(ctx, &ctx->part, ctx->part_cap);
-  if (rc == MG_OK) rc = dalloc(ctx, &ctx->part2, 256);
+  if (rc == MG_OK) rc = dalloc(ctx, &ctx->part2, kRedItems * kRedBlocks);
   if (rc == MG_OK) rc = dalloc(ctx, &ctx->part3, ctx->part_cap);
   if (rc == MG_OK) rc = dalloc(ctx, &ctx->part4, ctx->part_cap);
-  if (rc == MG_OK) rc = dalloc(ctx, &ctx->scal, 16);
   if (rc == MG_OK) {
     void* h = nullptr;
     if (hipHostMalloc(&h, 16 * sizeof(double), hipHostMallocDefault) != hipSuccess) rc = MG_EHIP;
@@ -3138,18 +3139,18 @@ void launch_force(mg_ctx* ctx, const Consts& C, const double* f, const double* p
   if (n % (4 * kFTX) == 0 && al16(f, out) && al16(pn)) {
     static_assert(kFTX * kFTY == kBlock, "one thread per 4-cell group of the tile");
     const unsigned tiles = (unsigned)((n / (4 * kFTX)) * (n / kFTY));
-    const unsigned nb = tiles * (unsigned)((n + kMarchKT - 1) / kMarchKT);
+    const int kt = march_depth(n, tiles);
+    const unsigned nb = tiles * (unsigned)((n + kt - 1) / kt);
     if (pn)
-      k_force_tile<true><<<nb, kBlock, 0, ctx->stream>>>(ctx->L[0], f, pn, sn, C, out, kMarchKT);
+      k_force_tile<true><<<nb, kBlock, 0, ctx->stream>>>(ctx->L[0], f, pn, sn, C, out, kt);
     else
-      k_force_tile<false><<<nb, kBlock, 0, ctx->stream>>>(ctx->L[0], f, nullptr, 0.0, C, out,
-                                                          kMarchKT);
+      k_force_tile<false><<<nb, kBlock, 0, ctx->stream>>>(ctx->L[0], f, nullptr, 0.0, C, out, kt);
   } else if (n % 4 == 0 && al16(f, out) && al16(pn)) {
     unsigned nchunk = (unsigned)(((int64_t)n * n / 4 + kBlock - 1) / kBlock);
-    unsigned nb = nchunk * (unsigned)((n + kMarchKT - 1) / kMarchKT);
-    if (pn) k_force_kv<true><<<nb, kBlock, 0, ctx->stream>>>(ctx->L[0], f, pn, sn, C, out, kMarchKT);
-    else k_force_kv<false><<<nb, kBlock, 0, ctx->stream>>>(ctx->L[0], f, nullptr, 0.0, C, out,
-                                                           kMarchKT);
+    const int kt = march_depth(n, nchunk);
+    unsigned nb = nchunk * (unsigned)((n + kt - 1) / kt);
+    if (pn) k_force_kv<true><<<nb, kBlock, 0, ctx->stream>>>(ctx->L[0], f, pn, sn, C, out, kt);
+    else k_force_kv<false><<<nb, kBlock, 0, ctx->stream>>>(ctx->L[0], f, nullptr, 0.0, C, out, kt);
   } else {
     if (pn) k_force<true><<<nblk(m), kBlock, 0, ctx->stream>>>(ctx->L[0], f, pn, sn, C, out);
     else k_force<false><<<nblk(m), kBlock, 0, ctx->stream>>>(ctx->L[0], f, nullptr, 0.0, C, out);
@@ -3317,9 +3318,10 @@ int mg_force_adjoint(mg_ctx* ctx, int model, const mg_model_params* params, cons
   int64_t m = (int64_t)n * n * n;
   if (n % (4 * kFTX) == 0 && al16(field, grad_force) && al16(grad_field_out)) {
     const unsigned tiles = (unsigned)((n / (4 * kFTX)) * (n / kFTY));
-    const unsigned nb = tiles * (unsigned)((n + kMarchKT - 1) / kMarchKT);
+    const int kt = march_depth(n, tiles);
+    const unsigned nb = tiles * (unsigned)((n + kt - 1) / kt);
     k_force_adjoint_tile<<<nb, kBlock, 0, ctx->stream>>>(ctx->L[0], field, grad_force, C,
-                                                         grad_field_out, kMarchKT);
+                                                         grad_field_out, kt);
   } else {
     k_force_adjoint<<<nblk(m), kBlock, 0, ctx->stream>>>(ctx->L[0], field, grad_force, C,
                                                          grad_field_out);
@@ -3370,7 +3372,7 @@ int mg_loss_force_sq(mg_ctx* ctx, const float* force, const int64_t* cellsv, int
     k_fill<float><<<nblk(3 * m), kBlock, 0, ctx->stream>>>(grad_force_out, 3 * m, 0.0f);
   k_loss_sq<<<nblk(n_cells), kBlock, 0, ctx->stream>>>(m, force, cellsv, n_cells, grad_force_out,
                                                        ctx->part);
-  ACHK(sum_on_device(ctx, nblk(n_cells), loss_out));
+  ACHK(reduce(ctx, {RedItem{ctx->part, loss_out, (int64_t)nblk(n_cells), 0}}));
   return MG_OK;
 }
 
