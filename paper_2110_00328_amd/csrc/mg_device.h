@@ -372,6 +372,42 @@ __device__ __forceinline__ float corr_G(const Consts& C, float h2, float ec, flo
   }
 }
 
+// Symmetron cell: e^3 + 3x e^2 + P e + Q = 0, P = m + 6 kap, Q = rho/s_amp -
+// kap sum, m = (1+delta) a*^3/a^3 - 1 + 3x^2, kap = c^2/(s_amp h^2); e holds the
+// linear guess, big asks for the closed form instead.
+struct SymCell {
+  float x, P, Q, e;
+  bool big;
+};
+__device__ __forceinline__ SymCell sym_cell(const Consts& C, float h2, float sum, float x, float dc,
+                                            float rho) {
+  SymCell c;
+  const float kap = C.f_ct2_samp * (1.0f / h2);
+  c.x = x;
+  c.P = sym_mass(C, x, dc) + mul_nc(6.0f, kap);
+  c.Q = __fmaf_rn(rho, C.f_isamp, -mul_nc(kap, sum));
+  c.e = f_div(-c.Q, c.P);
+  c.big = !(c.P > 0.0f && fabsf(c.Q) < mul_nc(mul_nc(1e-2f, c.P), fabsf(x)));
+  return c;
+}
+// total field y = x + e solves y^3 + p y + q = 0 (paper's branch)
+__device__ __forceinline__ float sym_large(const SymCell& c) {
+  const float p = c.P - mul_nc(c.x, mul_nc(3.0f, c.x));
+  const float q = __fmaf_rn(c.x, __fmaf_rn(c.x, c.x + c.x, -c.P), c.Q);
+  return (q < 0.0f ? cubic_root_approx(p, q) : cubic_root<float>(p, q)) - c.x;
+}
+__device__ __forceinline__ float sym_newton(const SymCell& c) {
+  const float x3 = mul_nc(3.0f, c.x), x6 = mul_nc(6.0f, c.x);
+  float e = c.e;
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {
+    const float g = __fmaf_rn(e, __fmaf_rn(e, e + x3, c.P), c.Q);
+    const float gp = __fmaf_rn(e, __fmaf_rn(e, 3.0f, x6), c.P);
+    if (gp != 0.0f) e = __fmaf_rn(-g, f_rcp(gp), e);
+  }
+  return e;
+}
+
 // Exact per-cell solve of G_c(e) = rho with the neighbours fixed.
 template <int M>
 __device__ __forceinline__ float corr_update(const Consts& C, float h2, float ec_old, float sum,
@@ -427,28 +463,9 @@ __device__ __forceinline__ float corr_update(const Consts& C, float h2, float ec
     }
     return x * sg * ((sg + 3.0f) * sg + 3.0f);
   } else if constexpr (M == SYM) {
-    // e^3 + 3x e^2 + P e + Q = 0, P = m + 6 kap, Q = rho/s_amp - kap sum,
-    // m = (1+delta) a*^3/a^3 - 1 + 3x^2, kap = c^2/(s_amp h^2)
-    float kap = C.f_ct2_samp * (1.0f / h2);
-    const float x3 = mul_nc(3.0f, x);
-    const float P = sym_mass(C, x, dc) + mul_nc(6.0f, kap);
-    const float Q = __fmaf_rn(rho, C.f_isamp, -mul_nc(kap, sum));
-    float e;
-    if (P > 0.0f && fabsf(Q) < 1e-2f * P * fabsf(x)) {
-      e = f_div(-Q, P);
-    } else {
-      // total field y = x + e solves y^3 + p y + q = 0 (paper's branch)
-      float p = P - mul_nc(x, x3);
-      float q = __fmaf_rn(x, __fmaf_rn(x, x + x, -P), Q);
-      e = (q < 0.0f ? cubic_root_approx(p, q) : cubic_root<float>(p, q)) - x;
-    }
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      const float g = __fmaf_rn(e, __fmaf_rn(e, e + x3, P), Q);
-      const float gp = __fmaf_rn(e, __fmaf_rn(e, 3.0f, mul_nc(6.0f, x)), P);
-      if (gp != 0.0f) e = __fmaf_rn(-g, f_rcp(gp), e);
-    }
-    return e;
+    SymCell c = sym_cell(C, h2, sum, x, dc, rho);
+    if (c.big) c.e = sym_large(c);
+    return sym_newton(c);
   } else {
     // Newton-Gauss-Seidel (eq:relaxation_iteration) on the correction
     float dn, dnp;

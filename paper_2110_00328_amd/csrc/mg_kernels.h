@@ -244,7 +244,21 @@ __device__ __forceinline__ void ld4s(const TS* __restrict__ p, float dec, float*
   } else {
     const nt_h4 v = __builtin_nontemporal_load(reinterpret_cast<const nt_h4*>(p));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) out[q] = float(v[q]) * dec;
+    for (int q = 0; q < 4; ++q) out[q] = mul_nc(float(v[q]), dec);
+  }
+}
+// sum += 4 consecutive stored cells, decoded and added in one rounding
+template <typename TS>
+__device__ __forceinline__ void add4s(const TS* __restrict__ p, float dec, float* sum) {
+  if constexpr (sizeof(TS) == 4) {
+    float v[4];
+    ldv_nt<float>(reinterpret_cast<const float*>(p), v);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[q] += v[q];
+  } else {
+    const nt_h4 v = __builtin_nontemporal_load(reinterpret_cast<const nt_h4*>(p));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[q] = __fmaf_rn(float(v[q]), dec, sum[q]);
   }
 }
 // float -> 4 consecutive stored cells (streaming store)
@@ -800,6 +814,16 @@ __device__ __forceinline__ void op_lin_resid_restrict(const Lev& Lf, const Lev& 
   eH[pc] = T(0);
 }
 
+// Constants with the Hu-Sawicki exponent known at compile time where N >= 0
+// (1, the usual one): the cell updates then hold no code, branches or
+// registers for the other exponents.  -1: any, taken from C.
+template <int M, int N>
+__device__ __forceinline__ Consts with_exponent(const Consts& c) {
+  Consts r = c;
+  if (M == FR && N >= 0) r.fr_n = N;
+  return r;
+}
+
 // ---------------------------------------------------------------------------
 // Vectorised grid kernels: V cells of one colour per thread (smoothers) or V
 // cells of each colour (residual kernels, so a row's two colours are read by
@@ -855,12 +879,13 @@ __device__ __forceinline__ void op_smooth_corr_v(const Lev& L, float* __restrict
   corr_update4<M>(C, h2, eo, sum, x, dc, r, out);
   stv_nt<float>(own + g, out);
 }
-template <int M, typename TX = float, typename TR = float>
+template <int M, int N, typename TX = float, typename TR = float>
 __global__ __launch_bounds__(kBlock) void k_smooth_corr_v(Lev L, float* e, const TX* X,
                                                           const float* dens, const TR* rho,
-                                                          int colour, float h2, Consts C,
+                                                          int colour, float h2, Consts C0,
                                                           int fresh, Store S = Store{1, 1, 1, 1}) {
   uint32_t g4 = (uint32_t)gid();
+  const Consts C = with_exponent<M, N>(C0);
   if (g4 < (uint32_t)(L.half / Vec<float>::V))
     op_smooth_corr_v<M, TX, TR>(L, e, X, dens, rho, colour, h2, C, g4, fresh, S);
 }
@@ -920,9 +945,14 @@ constexpr int kMarchKT = 16;  // planes per block on grids that fill the chip
 // 79 at 192^3 for CQ (123), 83 at 256^3 for the symmetron (102).
 constexpr unsigned kMarchMinBlocks = 1024;
 
+// c, ym, yp: offsets inside a plane of the thread's own cells and of the rows
+// j +- 1 (a plane of one colour holds n nh cells).  Planes are addressed as a
+// uniform k n nh plus these, so the marches multiply nothing per cell.
 struct MarchPos {
   int j, jm, jp, ih0, k0, k1;
+  uint32_t c, ym, yp, plane;
   bool ok;
+  __device__ __forceinline__ uint32_t at(int k) const { return (uint32_t)k * plane; }
 };
 __device__ __forceinline__ MarchPos march_pos(const Lev& L, int kt, int V) {
   MarchPos P;
@@ -940,6 +970,10 @@ __device__ __forceinline__ MarchPos march_pos(const Lev& L, int kt, int V) {
   P.jm = P.j == 0 ? L.n - 1 : P.j - 1;
   P.jp = P.j == L.n - 1 ? 0 : P.j + 1;
   P.k1 = P.k0 + kt < L.n ? P.k0 + kt : L.n;
+  P.plane = (uint32_t)L.n * (uint32_t)L.nh;
+  P.c = p;
+  P.ym = (uint32_t)P.jm * (uint32_t)L.nh + (uint32_t)P.ih0;
+  P.yp = (uint32_t)P.jp * (uint32_t)L.nh + (uint32_t)P.ih0;
   return P;
 }
 // blocks of a march over a level
@@ -973,39 +1007,39 @@ __device__ __forceinline__ void op_smooth_corr_kv(const Lev& L, float* e, const 
   const bool zero_nb = fresh && colour == 0;  // the other colour still holds no correction
   float zm[V] = {0, 0, 0, 0}, zc[V] = {0, 0, 0, 0}, zp[V] = {0, 0, 0, 0};
   if (!zero_nb) {
-    ldn<float, V>(o + prow(L, j, P.k0 == 0 ? n - 1 : P.k0 - 1) + ih0, zm);
-    ldn<float, V>(o + prow(L, j, P.k0) + ih0, zc);
+    ldn<float, V>(o + P.at(P.k0 == 0 ? n - 1 : P.k0 - 1) + P.c, zm);
+    ldn<float, V>(o + P.at(P.k0) + P.c, zc);
   }
   for (int k = P.k0; k < P.k1; ++k) {
-    const uint32_t r = prow(L, j, k);
+    const uint32_t pk = P.at(k), r = pk + P.c;  // the thread's first cell
     float sum[V] = {0, 0, 0, 0};
     if (!zero_nb) {
-      ldn<float, V>(o + prow(L, j, k + 1 == n ? 0 : k + 1) + ih0, zp);
+      ldn<float, V>(o + P.at(k + 1 == n ? 0 : k + 1) + P.c, zp);
       const int s = (j + k + colour) & 1;
       float xv[V + 1], ym[V], yp[V];
       if (s) {
 #pragma unroll
         for (int q = 0; q < V; ++q) xv[q] = zc[q];
-        xv[V] = o[r + (ih0 + V == L.nh ? 0 : ih0 + V)];
+        xv[V] = o[ih0 + V == L.nh ? r + V - L.nh : r + V];
       } else {
 #pragma unroll
         for (int q = 0; q < V; ++q) xv[q + 1] = zc[q];
-        xv[0] = o[r + (ih0 == 0 ? L.nh - 1 : ih0 - 1)];
+        xv[0] = o[ih0 == 0 ? r + L.nh - 1 : r - 1];
       }
-      ldn<float, V>(o + prow(L, P.jm, k) + ih0, ym);
-      ldn<float, V>(o + prow(L, P.jp, k) + ih0, yp);
+      ldn<float, V>(o + pk + P.ym, ym);
+      ldn<float, V>(o + pk + P.yp, yp);
 #pragma unroll
       for (int q = 0; q < V; ++q)
         sum[q] = (xv[q] + xv[q + 1]) + (ym[q] + yp[q]) + (zm[q] + zp[q]);
     }
-    const uint32_t q0 = (uint32_t)colour * (uint32_t)L.half + r + (uint32_t)ih0;
+    const uint32_t q0 = (uint32_t)colour * (uint32_t)L.half + r;
     float x[V], rr[V], dc[V] = {0, 0, 0, 0}, eo[V] = {0, 0, 0, 0}, out[V];
     ld4s<TX>(X + q0, S.x_dec, x);
     ld4s<TR>(rho + q0, S.r_dec, rr);
     if (M != FR) ldv_nt<float>(dens + q0, dc);
-    if (M == CQ && !fresh) ldv<float>(own + r + ih0, eo);
+    if (M == CQ && !fresh) ldv<float>(own + r, eo);
     corr_update4<M>(C, h2, eo, sum, x, dc, rr, out);
-    stv_nt<float>(own + r + ih0, out);
+    stv_nt<float>(own + r, out);
 #pragma unroll
     for (int q = 0; q < V; ++q) {
       zm[q] = zc[q];
@@ -1013,13 +1047,14 @@ __device__ __forceinline__ void op_smooth_corr_kv(const Lev& L, float* e, const 
     }
   }
 }
-template <int M, typename TX = float, typename TR = float>
+template <int M, int N, typename TX = float, typename TR = float>
 __global__ __launch_bounds__(kBlock) void k_smooth_corr_kv(Lev L, float* e, const TX* X,
                                                            const float* dens, const TR* rho,
                                                            int colour, float h2, Consts C,
                                                            int fresh, int kt,
                                                            Store S = Store{1, 1, 1, 1}) {
-  op_smooth_corr_kv<M, TX, TR>(L, e, X, dens, rho, colour, h2, C, fresh, kt, S);
+  op_smooth_corr_kv<M, TX, TR>(L, e, X, dens, rho, colour, h2, with_exponent<M, N>(C), fresh, kt,
+                               S);
 }
 // Exact per-cell update of the linear (adjoint) operator for 4 consecutive
 // packed cells at q0, given the sums of their 6 neighbours.
@@ -1050,35 +1085,35 @@ __global__ __launch_bounds__(kBlock) void k_smooth_lin_kv(Lev L, float* e, const
   const bool zero_nb = fresh && colour == 0;
   float zm[V] = {0, 0, 0, 0}, zc[V] = {0, 0, 0, 0}, zp[V] = {0, 0, 0, 0};
   if (!zero_nb) {
-    ldn<float, V>(o + prow(L, j, P.k0 == 0 ? n - 1 : P.k0 - 1) + ih0, zm);
-    ldn<float, V>(o + prow(L, j, P.k0) + ih0, zc);
+    ldn<float, V>(o + P.at(P.k0 == 0 ? n - 1 : P.k0 - 1) + P.c, zm);
+    ldn<float, V>(o + P.at(P.k0) + P.c, zc);
   }
   for (int k = P.k0; k < P.k1; ++k) {
-    const uint32_t rw = prow(L, j, k);
+    const uint32_t pk = P.at(k), rw = pk + P.c;  // the thread's first cell
     float sum[V] = {0, 0, 0, 0};
     if (!zero_nb) {
-      ldn<float, V>(o + prow(L, j, k + 1 == n ? 0 : k + 1) + ih0, zp);
+      ldn<float, V>(o + P.at(k + 1 == n ? 0 : k + 1) + P.c, zp);
       const int s = (j + k + colour) & 1;
       float xv[V + 1], ym[V], yp[V];
       if (s) {
 #pragma unroll
         for (int q = 0; q < V; ++q) xv[q] = zc[q];
-        xv[V] = o[rw + (ih0 + V == L.nh ? 0 : ih0 + V)];
+        xv[V] = o[ih0 + V == L.nh ? rw + V - L.nh : rw + V];
       } else {
 #pragma unroll
         for (int q = 0; q < V; ++q) xv[q + 1] = zc[q];
-        xv[0] = o[rw + (ih0 == 0 ? L.nh - 1 : ih0 - 1)];
+        xv[0] = o[ih0 == 0 ? rw + L.nh - 1 : rw - 1];
       }
-      ldn<float, V>(o + prow(L, P.jm, k) + ih0, ym);
-      ldn<float, V>(o + prow(L, P.jp, k) + ih0, yp);
+      ldn<float, V>(o + pk + P.ym, ym);
+      ldn<float, V>(o + pk + P.yp, yp);
 #pragma unroll
       for (int q = 0; q < V; ++q)
         sum[q] = (xv[q] + xv[q + 1]) + (ym[q] + yp[q]) + (zm[q] + zp[q]);
     }
-    const uint32_t q0 = (uint32_t)colour * (uint32_t)L.half + rw + (uint32_t)ih0;
+    const uint32_t q0 = (uint32_t)colour * (uint32_t)L.half + rw;
     float out[V];
     lin_update4<TD, TR>(dg, r, q0, kh2, S, sum, out);
-    stv_nt<float>(own + rw + ih0, out);
+    stv_nt<float>(own + rw, out);
 #pragma unroll
     for (int q = 0; q < V; ++q) {
       zm[q] = zc[q];
@@ -1092,9 +1127,9 @@ __global__ __launch_bounds__(kBlock) void k_smooth_lin_kv(Lev L, float* e, const
 // of colour c in row (j, k)
 template <typename TE, int V>
 __device__ __forceinline__ void march_ld(const Lev& L, const double* __restrict__ w,
-                                         const TE* __restrict__ e, int c, int j, int k, int ih0,
+                                         const TE* __restrict__ e, int c, uint32_t off,
                                          double* out, double wu) {
-  const uint32_t q0 = (uint32_t)c * (uint32_t)L.half + prow(L, j, k) + (uint32_t)ih0;
+  const uint32_t q0 = (uint32_t)c * (uint32_t)L.half + off;
   if (w) {
     ldn<double, V>(w + q0, out);
   } else {
@@ -1118,11 +1153,12 @@ __device__ __forceinline__ void march_nbsum(const Lev& L, const double* __restri
   const int o = 1 - c;
   const int s = (P.j + k + c) & 1;
   double ym[V], yp[V];
-  march_ld<TE, V>(L, w, e, o, P.jm, k, P.ih0, ym, wu);
-  march_ld<TE, V>(L, w, e, o, P.jp, k, P.ih0, yp, wu);
-  const uint32_t ro = (uint32_t)o * (uint32_t)L.half + prow(L, P.j, k);
-  const uint32_t xi = s ? (P.ih0 + V == L.nh ? 0 : P.ih0 + V) : (P.ih0 == 0 ? L.nh - 1 : P.ih0 - 1);
-  const double xe = (w ? w[ro + xi] : wu) + (e ? double(e[ro + xi]) : 0.0);
+  march_ld<TE, V>(L, w, e, o, P.at(k) + P.ym, ym, wu);
+  march_ld<TE, V>(L, w, e, o, P.at(k) + P.yp, yp, wu);
+  const uint32_t ro = (uint32_t)o * (uint32_t)L.half + P.at(k) + P.c;  // cell ih0 of the row
+  const uint32_t xi = s ? (P.ih0 + V == L.nh ? ro + V - L.nh : ro + V)
+                        : (P.ih0 == 0 ? ro + L.nh - 1 : ro - 1);
+  const double xe = (w ? w[xi] : wu) + (e ? double(e[xi]) : 0.0);
   double xv[V + 1];
 #pragma unroll
   for (int t = 0; t < V; ++t) xv[s ? t : t + 1] = wo[1][t];
@@ -1132,12 +1168,12 @@ __device__ __forceinline__ void march_nbsum(const Lev& L, const double* __restri
     sum[q] = (xv[q] + xv[q + 1]) + (ym[q] + yp[q]) + (wo[0][q] + wo[2][q]);
 }
 
-template <int M, typename TX = float, typename TR = float>
+template <int M, int N, typename TX = float, typename TR = float>
 __global__ __launch_bounds__(kBlock) void k_outer_fused_kv(Lev L, const double* __restrict__ w,
                                                            const float* __restrict__ e,
                                                            double* __restrict__ w_new,
                                                            const float* __restrict__ dens,
-                                                           Consts C, TR* __restrict__ rho,
+                                                           Consts C0, TR* __restrict__ rho,
                                                            TX* __restrict__ X,
                                                            float* __restrict__ e_zero,
                                                            double* __restrict__ part,
@@ -1146,6 +1182,7 @@ __global__ __launch_bounds__(kBlock) void k_outer_fused_kv(Lev L, const double* 
                                                            double* __restrict__ part_max = nullptr) {
   constexpr int V = kVOuter;
   static_assert(V == 4, "the stored 4-cell groups");
+  const Consts C = with_exponent<M, N>(C0);
   __shared__ double sh[32];
   const MarchPos P = march_pos(L, kt, V);
   double acc = 0.0, accb = 0.0;  // sum d^2; sum (bg_coef delta)^2 when part_bg is given
@@ -1156,18 +1193,18 @@ __global__ __launch_bounds__(kBlock) void k_outer_fused_kv(Lev L, const double* 
     const double wu = C.bg;  // w null: the master is the uniform background
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      march_ld<float, V>(L, w, e, c, P.j, km0, P.ih0, win[c][0], wu);
-      march_ld<float, V>(L, w, e, c, P.j, P.k0, P.ih0, win[c][1], wu);
+      march_ld<float, V>(L, w, e, c, P.at(km0) + P.c, win[c][0], wu);
+      march_ld<float, V>(L, w, e, c, P.at(P.k0) + P.c, win[c][1], wu);
     }
     for (int k = P.k0; k < P.k1; ++k) {
       const int kp = k + 1 == L.n ? 0 : k + 1;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) march_ld<float, V>(L, w, e, c, P.j, kp, P.ih0, win[c][2], wu);
+      for (int c = 0; c < 2; ++c) march_ld<float, V>(L, w, e, c, P.at(kp) + P.c, win[c][2], wu);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         double sum[V];
         march_nbsum<float, V>(L, w, e, P, c, k, win[1 - c], sum, wu);
-        const uint32_t q0 = (uint32_t)c * (uint32_t)L.half + prow(L, P.j, k) + (uint32_t)P.ih0;
+        const uint32_t q0 = (uint32_t)c * (uint32_t)L.half + P.at(k) + P.c;
         if (e) stn_nt<double, V>(w_new + q0, win[c][1]);
         float dn[V], ro[V], xo[V], zo[V];
         ldn_nt<float, V>(dens + q0, dn);
@@ -1230,18 +1267,18 @@ __global__ __launch_bounds__(kBlock) void k_lin_outer_fused_kv(
     const int km0 = P.k0 == 0 ? L.n - 1 : P.k0 - 1;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {  // lam null: lam = 0
-      march_ld<TO, V>(L, lam, e, c, P.j, km0, P.ih0, win[c][0], 0.0);
-      march_ld<TO, V>(L, lam, e, c, P.j, P.k0, P.ih0, win[c][1], 0.0);
+      march_ld<TO, V>(L, lam, e, c, P.at(km0) + P.c, win[c][0], 0.0);
+      march_ld<TO, V>(L, lam, e, c, P.at(P.k0) + P.c, win[c][1], 0.0);
     }
     for (int k = P.k0; k < P.k1; ++k) {
       const int kp = k + 1 == L.n ? 0 : k + 1;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) march_ld<TO, V>(L, lam, e, c, P.j, kp, P.ih0, win[c][2], 0.0);
+      for (int c = 0; c < 2; ++c) march_ld<TO, V>(L, lam, e, c, P.at(kp) + P.c, win[c][2], 0.0);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         double sum[V], lc[V], dd[V], bb[V];
         march_nbsum<TO, V>(L, lam, e, P, c, k, win[1 - c], sum, 0.0);
-        const uint32_t q0 = (uint32_t)c * (uint32_t)L.half + prow(L, P.j, k) + (uint32_t)P.ih0;
+        const uint32_t q0 = (uint32_t)c * (uint32_t)L.half + P.at(k) + P.c;
 #pragma unroll
         for (int q = 0; q < V; ++q) {
           lc[q] = win[c][1][q] + shift;
@@ -1528,7 +1565,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong_kv(Lev Lf, Lev Lc, T* __rest
 
 // ---------------------------------------------------------------------------
 // Prolongation fused into the first post-smoothing half-sweep of a smoother
-// that solves each cell exactly (f(R), symmetron, the linear adjoint).
+// that solves each cell exactly (f(R), the linear adjoint).
 // There the prolonged colour-1 values e1 + P(c - c2) are read only as the
 // neighbours of the colour-0 half-sweep: the colour-1 half-sweep after it
 // overwrites e1 without reading it (and the colour-0 prolongation is not
@@ -1571,19 +1608,17 @@ __device__ __forceinline__ void dec4s(const Raw4<TS>& r, float dec, float* out) 
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     if constexpr (sizeof(TS) == 4) out[q] = r.v[q];
-    else out[q] = float(r.v[q]) * dec;
+    else out[q] = mul_nc(float(r.v[q]), dec);
   }
 }
 // Cell update policies for four consecutive colour-0 cells at packed index
-// q0: load() the cell data, apply() the update to the neighbour sums.
-// kPreload: load a step's cell data before the LDS exchange (f(R), linear:
-// 31.3 against 31.7 ms per 512^3 f(R) step); the symmetron's extra density
-// operand would cost a wave per SIMD, so it loads after the exchange.
+// q0: load() the cell data, apply() the update to the neighbour sums.  A
+// step's cell data are loaded before the LDS exchange (31.3 against 31.7 ms
+// per 512^3 f(R) step).
 template <int M, typename TX, typename TR>
 struct UpdCorr {
-  static constexpr bool kPreload = M != SYM;
+  static_assert(M == FR, "the density operand is not loaded");
   const TX* X;
-  const float* dens;
   const TR* rho;
   float h2;
   Store S;
@@ -1591,26 +1626,22 @@ struct UpdCorr {
   struct In {
     Raw4<TX> x;
     Raw4<TR> r;
-    Raw4<float> d;
   };
   __device__ __forceinline__ In load(uint32_t q0) const {
     In a;
     a.x = ld4raw<TX>(X + q0);
     a.r = ld4raw<TR>(rho + q0);
-    if (M != FR) a.d = ld4raw<float>(dens + q0);
     return a;
   }
   __device__ __forceinline__ void apply(const In& a, const float* sum, float* out) const {
     float x[4], rr[4], dc[4] = {0, 0, 0, 0}, eo[4] = {0, 0, 0, 0};
     dec4s<TX>(a.x, S.x_dec, x);
     dec4s<TR>(a.r, S.r_dec, rr);
-    if (M != FR) dec4s<float>(a.d, 1.0f, dc);
     corr_update4<M>(C, h2, eo, sum, x, dc, rr, out);
   }
 };
 template <typename TD, typename TR>
 struct UpdLin {
-  static constexpr bool kPreload = true;
   const TD* dg;
   const TR* r;
   float kh2;
@@ -1731,13 +1762,10 @@ __global__ __launch_bounds__(kBlock) void k_prolong_smooth0(Lev Lf, Lev Lc, floa
     const int Kn = K + 1 == nc ? 0 : K + 1;
     const int k0 = 2 * K, k1 = 2 * K + 1, k2 = 2 * Kn;
     typename U::In in[2][2];  // cell data of the two planes' own rows
-    if constexpr (U::kPreload) {
 #pragma unroll
-      for (int z = 0; z < 2; ++z)
+    for (int z = 0; z < 2; ++z)
 #pragma unroll
-        for (int y = 0; y < 2; ++y)
-          in[z][y] = upd.load(prow(Lf, 2 * Jr + y, k0 + z) + (uint32_t)I0);
-    }
+      for (int y = 0; y < 2; ++y) in[z][y] = upd.load(prow(Lf, 2 * Jr + y, k0 + z) + (uint32_t)I0);
     prolong_plane_h(Lc, c, c2, I0, Js, Kn, first, aN, hN);
     float Ed[2][4], Edh[4], Ee[2][4], Eeh[4];
     own_rows(k1, aK, aN, Ed);  // child z = 1 of plane K
@@ -1798,7 +1826,6 @@ __global__ __launch_bounds__(kBlock) void k_prolong_smooth0(Lev Lf, Lev Lc, floa
           for (int q = 0; q < 4; ++q)
             sum[q] = (xv[q] + xv[q + 1]) + (ym[q] + yp[q]) + (zmv[y][q] + zpv[y][q]);
           const uint32_t r = prow(Lf, j, k) + (uint32_t)I0;
-          if constexpr (!U::kPreload) in[z][y] = upd.load(r);
           upd.apply(in[z][y], sum, out);
           stv_nt<float>(e + r, out);
         }
@@ -1849,11 +1876,7 @@ __device__ __forceinline__ void op_resid_restrict_corr_v(
         if (col == 1 && skip1) {
 #pragma unroll
           for (int q = 0; q < V; ++q) se[q] += ec[q];
-          if (want_x) {
-            ld4s<TX>(X + q0, S.x_dec, x);
-#pragma unroll
-            for (int q = 0; q < V; ++q) sx[q] += x[q];
-          }
+          if (want_x) add4s<TX>(X + q0, S.x_dec, sx);
           continue;
         }
         nbsum_vec<float>(Lf, e + (1 - col) * Lf.half, I0, j, k, (j + k + col) & 1, sum);
@@ -1872,7 +1895,7 @@ __device__ __forceinline__ void op_resid_restrict_corr_v(
   for (int q = 0; q < V; ++q)
     store_coarse_corr(pk_of(Lc, I0 + q, J, K), se[q], sd[q], sx[q], eH, eR, rhoH, XH, Xf, rx);
 }
-template <int M, typename TX = float, typename TR = float>
+template <int M, int N, typename TX = float, typename TR = float>
 __global__ __launch_bounds__(kBlock) void k_resid_restrict_corr_v(
     Lev Lf, Lev Lc, const float* __restrict__ e, const TX* __restrict__ X,
     const float* __restrict__ dens, const TR* __restrict__ rho, float h2, float* eH, float* eR,
@@ -1880,8 +1903,8 @@ __global__ __launch_bounds__(kBlock) void k_resid_restrict_corr_v(
     float* Xf = nullptr, int rx = 0) {
   uint32_t g4 = (uint32_t)gid();
   if (g4 < (uint32_t)(2 * Lc.half / Vec<float>::V))
-    op_resid_restrict_corr_v<M, TX, TR>(Lf, Lc, e, X, dens, rho, h2, eH, eR, rhoH, XH, C, skip1,
-                                        g4, S, Xf, rx);
+    op_resid_restrict_corr_v<M, TX, TR>(Lf, Lc, e, X, dens, rho, h2, eH, eR, rhoH, XH,
+                                        with_exponent<M, N>(C), skip1, g4, S, Xf, rx);
 }
 
 // Residual and restriction marching in z, for exact per-cell smoothers
@@ -2001,13 +2024,14 @@ __device__ __forceinline__ RRPos rr_pos(const Lev& Lc, int kt) {
   P.K1 = P.K0 + kt < nc ? P.K0 + kt : nc;
   return P;
 }
-template <int M, typename TX = float, typename TR = float>
+template <int M, int N, typename TX = float, typename TR = float>
 __global__ __launch_bounds__(kBlock) void k_resid_restrict_corr_kv(
     Lev Lf, Lev Lc, const float* __restrict__ e, const TX* __restrict__ X,
     const float* __restrict__ dens, const TR* __restrict__ rho, float h2,
     float* __restrict__ eH, float* __restrict__ eR, float* __restrict__ rhoH,
-    float* __restrict__ XH, Consts C, int kt, Store S = Store{1, 1, 1, 1}, float* Xf = nullptr,
+    float* __restrict__ XH, Consts C0, int kt, Store S = Store{1, 1, 1, 1}, float* Xf = nullptr,
     int rx = 0) {
+  const Consts C = with_exponent<M, N>(C0);
   const RRPos P = rr_pos(Lc, kt);
   if (!P.ok) return;
   const int n = Lf.n, I0 = P.I0, J = P.J;
@@ -2058,11 +2082,7 @@ __global__ __launch_bounds__(kBlock) void k_resid_restrict_corr_kv(
         // colour 1: restricted only
 #pragma unroll
         for (int q = 0; q < 4; ++q) se[q] += cen[q];
-        if (want_x) {
-          ld4s<TX>(X + Lf.half + q0, S.x_dec, x);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) sx[q] += x[q];
-        }
+        if (want_x) add4s<TX>(X + Lf.half + q0, S.x_dec, sx);
       }
     }
     // coarse outputs as in store_coarse_corr, 4 natural cells at a time
@@ -2726,15 +2746,6 @@ template <typename T>
 struct SmallCell {
   T a, b, d;
 };
-// N: the Hu-Sawicki exponent when known at compile time (1, the usual one),
-// else -1: a launch runs every instruction but a few times, from a cold
-// instruction cache, so the code of the other exponents is left out
-template <int M, int N>
-__device__ __forceinline__ Consts small_consts(const Consts& c) {
-  Consts r = c;
-  if (M == FR && N >= 0) r.fr_n = N;
-  return r;
-}
 template <int M>
 struct SmallCorr {
   typedef float T;
@@ -3089,13 +3100,13 @@ __global__ __launch_bounds__(kFusedThreads) void k_small_direct(FusedDirect<doub
                                                                 FusedProg G, Consts C) {
   extern __shared__ __align__(16) unsigned char small_lds[];
   __shared__ double sh[48];
-  small_cycle(F, G, SmallDirect<M>{small_consts<M, N>(C)}, reinterpret_cast<double*>(small_lds), sh);
+  small_cycle(F, G, SmallDirect<M>{with_exponent<M, N>(C)}, reinterpret_cast<double*>(small_lds), sh);
 }
 template <int M, int N>
 __global__ __launch_bounds__(kFusedThreads) void k_small_corr(FusedCorr F, FusedProg G, Consts C) {
   extern __shared__ __align__(16) unsigned char small_lds[];
   __shared__ double sh[48];
-  small_cycle(F, G, SmallCorr<M>{small_consts<M, N>(C)}, reinterpret_cast<float*>(small_lds), sh);
+  small_cycle(F, G, SmallCorr<M>{with_exponent<M, N>(C)}, reinterpret_cast<float*>(small_lds), sh);
 }
 template <typename T>
 __global__ __launch_bounds__(kFusedThreads) void k_small_lin(FusedLin<T> F, FusedProg G) {

@@ -763,10 +763,15 @@ int make_prog(mg_ctx* ctx, int l, const mg_solver_opts* o, int type, FusedProg* 
 
 // Calls fn with the f(R) exponent as a compile-time constant: 1, or -1 for
 // any (the kernel then takes it from C).
-template <typename Fn>
-void launch_small(const Consts& C, Fn&& fn) {
-  if (C.model == FR && C.fr_n == 1) fn(std::integral_constant<int, 1>{});
-  else fn(std::integral_constant<int, -1>{});
+template <int M, typename Fn>
+void with_n(const Consts& C, Fn&& fn) {
+  if constexpr (M == FR) {
+    if (C.fr_n == 1) {
+      fn(std::integral_constant<int, 1>{});
+      return;
+    }
+  }
+  fn(std::integral_constant<int, -1>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -820,7 +825,7 @@ int cycle64(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
     FusedProg P;
     ACHK(make_prog(ctx, l, o, type, &P));
     if (F.L[0].n <= kSmallN)
-      launch_small(C, [&](auto N) {
+      with_n<M>(C, [&](auto N) {
         k_small_direct<M, N><<<1, kFusedThreads, small_lds_bytes<SmallDirect<M>>(F.L, F.nlev),
                                ctx->stream>>>(F, P, C);
       });
@@ -1034,16 +1039,20 @@ int smooth32(mg_ctx* ctx, const Consts& C, int l, int sweeps, bool fresh = false
         with_level_store(ctx, l, [&](auto* X, auto* R) {
           using TX = std::remove_pointer_t<decltype(X)>;
           using TR = std::remove_pointer_t<decltype(R)>;
-          k_smooth_corr_kv<M, TX, TR>
-              <<<march_blocks(L, kt, Vec<float>::V), kBlock, 0, ctx->stream>>>(
-                  L, W.e[l], X, W.dens[l], R, colour, float(lev_h2(l)), C, fr, kt, S);
+          with_n<M>(C, [&](auto N) {
+            k_smooth_corr_kv<M, N, TX, TR>
+                <<<march_blocks(L, kt, Vec<float>::V), kBlock, 0, ctx->stream>>>(
+                    L, W.e[l], X, W.dens[l], R, colour, float(lev_h2(l)), C, fr, kt, S);
+          });
         });
       else if (vec)
         with_level_store(ctx, l, [&](auto* X, auto* R) {
           using TX = std::remove_pointer_t<decltype(X)>;
           using TR = std::remove_pointer_t<decltype(R)>;
-          k_smooth_corr_v<M, TX, TR><<<nblk(nv), kBlock, 0, ctx->stream>>>(
-              L, W.e[l], X, W.dens[l], R, colour, float(lev_h2(l)), C, fr, S);
+          with_n<M>(C, [&](auto N) {
+            k_smooth_corr_v<M, N, TX, TR><<<nblk(nv), kBlock, 0, ctx->stream>>>(
+                L, W.e[l], X, W.dens[l], R, colour, float(lev_h2(l)), C, fr, S);
+          });
         });
       else
         k_smooth_corr<M><<<nblk(L.half), kBlock, 0, ctx->stream>>>(L, W.e[l], W.X[l], W.dens[l],
@@ -1104,7 +1113,7 @@ int cycle32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
     FusedProg P;
     ACHK(make_prog(ctx, l, o, type, &P, rx ? 1 : 0));
     if (F.L[0].n <= kSmallN)
-      launch_small(C, [&](auto N) {
+      with_n<M>(C, [&](auto N) {
         k_small_corr<M, N><<<1, kFusedThreads, small_lds_bytes<SmallCorr<M>>(F.L, F.nlev),
                              ctx->stream>>>(F, P, C);
       });
@@ -1142,18 +1151,22 @@ int cycle32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
     with_level_store(ctx, l, [&](auto* X, auto* R) {
       using TX = std::remove_pointer_t<decltype(X)>;
       using TR = std::remove_pointer_t<decltype(R)>;
-      k_resid_restrict_corr_kv<M, TX, TR>
-          <<<prolong_march_blocks(Lc.n, kRestrictKT), kBlock, 0, ctx->stream>>>(
-              Lf, Lc, W.e[l], X, W.dens[l], R, float(lev_h2(l)), ezero, (float*)nullptr,
-              W.rho[l + 1], W.X[l + 1], C, kRestrictKT, S, Xf, rxi);
+      with_n<M>(C, [&](auto N) {
+        k_resid_restrict_corr_kv<M, N, TX, TR>
+            <<<prolong_march_blocks(Lc.n, kRestrictKT), kBlock, 0, ctx->stream>>>(
+                Lf, Lc, W.e[l], X, W.dens[l], R, float(lev_h2(l)), ezero, (float*)nullptr,
+                W.rho[l + 1], W.X[l + 1], C, kRestrictKT, S, Xf, rxi);
+      });
     });
   else if (vec)
     with_level_store(ctx, l, [&](auto* X, auto* R) {
       using TX = std::remove_pointer_t<decltype(X)>;
       using TR = std::remove_pointer_t<decltype(R)>;
-      k_resid_restrict_corr_v<M, TX, TR><<<nblk(ncv), kBlock, 0, ctx->stream>>>(
-          Lf, Lc, W.e[l], X, W.dens[l], R, float(lev_h2(l)), ezero, (float*)nullptr,
-          W.rho[l + 1], W.X[l + 1], C, skip1, S, Xf, rxi);
+      with_n<M>(C, [&](auto N) {
+        k_resid_restrict_corr_v<M, N, TX, TR><<<nblk(ncv), kBlock, 0, ctx->stream>>>(
+            Lf, Lc, W.e[l], X, W.dens[l], R, float(lev_h2(l)), ezero, (float*)nullptr,
+            W.rho[l + 1], W.X[l + 1], C, skip1, S, Xf, rxi);
+      });
     });
   else
     k_resid_restrict_corr<M><<<nblk(cells(Lc)), kBlock, 0, ctx->stream>>>(
@@ -1172,17 +1185,21 @@ int cycle32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
     ACHK(cycle32<M>(ctx, C, o, l + 1, MG_CYCLE_F, true, cfresh));
     ACHK(cycle32<M>(ctx, C, o, l + 1, MG_CYCLE_V, false));
   }
-  if (M != CQ && vec && fuse_prolong(ctx, l)) {
-    // e += P e_H formed inside the first colour-0 half-sweep
-    with_level_store(ctx, l, [&](auto* X, auto* R) {
-      using TX = std::remove_pointer_t<decltype(X)>;
-      using TR = std::remove_pointer_t<decltype(R)>;
-      const UpdCorr<M, TX, TR> U{X, W.dens[l], R, float(lev_h2(l)), level_store(ctx, l), C};
-      launch_prolong_smooth0(ctx, l, W.e[l], W.e[l + 1], (const float*)nullptr, U);
-    });
-    LAUNCHCHK();
-    return smooth32<M>(ctx, C, l, o->nu_post, false, true);
-  }
+  // f(R) only: the symmetron's closed form, inlined for each of the kernel's 16
+  // cells, makes it slower than the two kernels (77 us against 15 + 30 at
+  // 256^3 with clumps)
+  if constexpr (M == FR)
+    if (vec && fuse_prolong(ctx, l)) {
+      // e += P e_H formed inside the first colour-0 half-sweep
+      with_level_store(ctx, l, [&](auto* X, auto* R) {
+        using TX = std::remove_pointer_t<decltype(X)>;
+        using TR = std::remove_pointer_t<decltype(R)>;
+        const UpdCorr<M, TX, TR> U{X, R, float(lev_h2(l)), level_store(ctx, l), C};
+        launch_prolong_smooth0(ctx, l, W.e[l], W.e[l + 1], (const float*)nullptr, U);
+      });
+      LAUNCHCHK();
+      return smooth32<M>(ctx, C, l, o->nu_post, false, true);
+    }
   if (vec) {
     // e += P e_H; colour 0 too only for the Newton (CQ) smoother
     launch_prolong<float, M == CQ ? 0 : 1>(ctx, Lf, Lc, W.e[l], W.e[l + 1], (const float*)nullptr);
@@ -1285,9 +1302,11 @@ int solve32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const float* 
         with_level_store(ctx, 0, [&](auto* X, auto* R) {
           using TX = std::remove_pointer_t<decltype(X)>;
           using TR = std::remove_pointer_t<decltype(R)>;
-          k_outer_fused_kv<M, TX, TR><<<(unsigned)nparts, kBlock, 0, ctx->stream>>>(
-              L0, wsrc, pending, wn, W.dens[0], C, R, X, ez, ctx->part,
-              bgsum ? ctx->part3 : nullptr, mkt, ctx->s0.S, r16 ? ctx->part4 : nullptr);
+          with_n<M>(C, [&](auto N) {
+            k_outer_fused_kv<M, N, TX, TR><<<(unsigned)nparts, kBlock, 0, ctx->stream>>>(
+                L0, wsrc, pending, wn, W.dens[0], C, R, X, ez, ctx->part,
+                bgsum ? ctx->part3 : nullptr, mkt, ctx->s0.S, r16 ? ctx->part4 : nullptr);
+          });
         });
         LAUNCHCHK();
         double mx = 0.0;
