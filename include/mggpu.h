@@ -119,7 +119,11 @@ typedef struct mg_ctx mg_ctx;
  * first post-smoothing half-sweep of the f(R), symmetron and linear
  * (adjoint) FP32 cycles, used on the levels where its grid reaches
  * MGGPU_PROLONG_SMOOTH_MIN_BLOCKS workgroups (default 512; the depth is
- * halved to reach it), and
+ * halved to reach it),
+ * MGGPU_MID_MAX_N sets up to how many cells a side a level of the f(R),
+ * symmetron and adjoint FP32 V(1,1) cycles runs its way down and its way up in
+ * one launch each (default and maximum 80; 0: separate kernels; identical
+ * results), and
  * MGGPU_FP16_STORAGE=0 keeps the finest level's X and rho of the
  * FP32-refined solve in FP32 instead of 16-bit floats (default 1; n % 8 == 0
  * grids; changes rounding inside the FP32 correction cycles only, the FP64

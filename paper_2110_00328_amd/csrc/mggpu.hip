@@ -28,6 +28,7 @@
 #include "mg_batched.h"
 #include "mg_grouped.h"
 #include "mg_kernels.h"
+#include "mg_mid.h"
 #include "mggpu.h"
 
 using namespace mgg;
@@ -57,6 +58,7 @@ struct Work32 {  // FP32 correction mode
   // linearisation point (the coarse problem's fixed part); levels inside the
   // single-workgroup kernel: R e of the finer level
   float* eR[kMaxLev] = {};
+  float* ea[kMaxLev] = {};     // middle levels: colour 1 between the way down and the way up
   h16* X16 = nullptr;          // level-0 X in 16 bits (when the context stores 16-bit data)
   h16* R16 = nullptr;          // level-0 rho in 16 bits
 };
@@ -66,6 +68,7 @@ struct WorkLin {  // adjoint linear multigrid in precision T
   T* e[kMaxLev] = {};
   T* r[kMaxLev] = {};
   T* dg[kMaxLev] = {};
+  T* ea[kMaxLev] = {};  // as Work32's (FP32 solve only)
   h16* dg16 = nullptr;  // level-0 dg and r in 16 bits (FP32 solve only)
   h16* r16 = nullptr;
 };
@@ -113,6 +116,10 @@ struct mg_ctx {
   // method; another value forces the divergence path from the host in tests;
   // MGGPU_TEST_CORRECTION_SCALE overrides it at context creation)
   float test_escale = 1.0f;
+  // levels of at most this many cells a side (never more than kMidMaxN) run
+  // their way down and their way up in one launch each (mg_mid.h);
+  // MGGPU_MID_MAX_N at context creation lowers it (0: one kernel per operation)
+  int mid_max_n = kMidMaxN;
   // set while mg_solve_noalloc runs on the static scratch array: any device
   // allocation is then an error instead
   bool noalloc = false;
@@ -315,6 +322,7 @@ int ensure32(mg_ctx* ctx) {
     ACHK(dalloc(ctx, &W.rho[l], m));
     ACHK(dalloc(ctx, &W.dens[l], m));
     if (l > 0) ACHK(dalloc(ctx, &W.eR[l], m));
+    if (l < ctx->fused_from && ctx->L[l].n <= kMidMaxN) ACHK(dalloc(ctx, &W.ea[l], m / 2));
   }
   ACHK(dalloc(ctx, &W.X16, cells(ctx->L[0])));
   ACHK(dalloc(ctx, &W.R16, cells(ctx->L[0])));
@@ -365,6 +373,8 @@ int ensure_lin(mg_ctx* ctx, WorkLin<T>& W) {
     ACHK(dalloc(ctx, &W.e[l], m));
     ACHK(dalloc(ctx, &W.r[l], m));
     if (l > 0 || sizeof(T) == 4) ACHK(dalloc(ctx, &W.dg[l], m));
+    if (sizeof(T) == 4 && l < ctx->fused_from && ctx->L[l].n <= kMidMaxN)
+      ACHK(dalloc(ctx, &W.ea[l], m / 2));
   }
   W.ebuf[0] = W.e[0];
   ACHK(dalloc(ctx, &W.ebuf[1], cells(ctx->L[0])));
@@ -1090,6 +1100,14 @@ void launch_prolong_smooth0(mg_ctx* ctx, int l, float* e, const float* c, const 
   k_prolong_smooth0<U><<<ntile * nz, R * (Lc.n / 4), 0, ctx->stream>>>(Lf, Lc, e, c, c2, kt, upd);
 }
 
+// Level l runs its way down and up in one launch each: one sweep before and
+// after, exact per-cell smoother (the caller's matter), few enough cells.  Not
+// on a timed finest level, whose half-sweeps mg_prof_read reports.
+bool use_mid(const mg_ctx* ctx, const mg_solver_opts* o, int l) {
+  return ctx->L[l].n <= ctx->mid_max_n && l + 1 < ctx->nlev && l < ctx->fused_from &&
+         o->nu_pre == 1 && o->nu_post == 1 && !(l == 0 && ctx->prof);
+}
+
 // rx: restrict the linearisation point X on the way down (first cycle of
 // an outer step)
 template <int M>
@@ -1125,7 +1143,8 @@ int cycle32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
   if (l == ctx->nlev - 1) return smooth32<M>(ctx, C, l, single_level_sweeps(ctx, o), fresh);
   const Lev& Lf = ctx->L[l];
   const Lev& Lc = ctx->L[l + 1];
-  ACHK(smooth32<M>(ctx, C, l, o->nu_pre, fresh));
+  const bool mid = M != CQ && use_mid(ctx, o, l);
+  if (!mid) ACHK(smooth32<M>(ctx, C, l, o->nu_pre, fresh));
   const bool vec = Lc.n % Vec<float>::V == 0;
   const int64_t ncv = cells(Lc) / Vec<float>::V;
   // exact per-cell smoothers (f(R), symmetron): the colour swept last has
@@ -1141,13 +1160,30 @@ int cycle32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
   // vectorised smoother that sweeps before anything reads e); elsewhere the
   // restriction writes zeros.
   const Lev& Lc1 = ctx->L[l + 1];
-  const bool cfresh = l + 1 < ctx->fused_from && Lc1.nh % Vec<float>::V == 0 &&
+  const bool cfresh = l + 1 < ctx->fused_from &&
+                      (Lc1.nh % Vec<float>::V == 0 || (M != CQ && use_mid(ctx, o, l + 1))) &&
                       (o->nu_pre > 0 || l + 1 == ctx->nlev - 1);
   float* ezero = cfresh ? (float*)nullptr : W.e[l + 1];
   float* Xf = W.eR[l + 1];
   const int rxi = rx ? 1 : 0;
-  if (skip1 && Lc.n % 4 == 0 && Lc.n >= 8 &&
-      prolong_march_blocks(Lc.n, kRestrictKT) >= ctx->march_min_blocks)
+  // launches fn(policy) with the level's cell data for the one-launch kernels
+  auto with_mid = [&](auto&& fn) {
+    if constexpr (M != CQ)
+      with_level_store(ctx, l, [&](auto* X, auto* R) {
+        using TX = std::remove_pointer_t<decltype(X)>;
+        using TR = std::remove_pointer_t<decltype(R)>;
+        with_n<M>(C, [&](auto N) {
+          fn(MidCorr<M, N, TX, TR>{X, R, W.dens[l], float(lev_h2(l)), S, C});
+        });
+      });
+  };
+  if (mid)
+    with_mid([&](const auto& P) {
+      k_mid_down<<<mid_blocks(Lf), kMidThreads, mid_down_lds(Lf), ctx->stream>>>(
+          Lf, Lc, P, W.e[l], W.ea[l], ezero, W.rho[l + 1], W.X[l + 1], Xf, rxi, fresh ? 1 : 0);
+    });
+  else if (skip1 && Lc.n % 4 == 0 && Lc.n >= 8 &&
+           prolong_march_blocks(Lc.n, kRestrictKT) >= ctx->march_min_blocks)
     with_level_store(ctx, l, [&](auto* X, auto* R) {
       using TX = std::remove_pointer_t<decltype(X)>;
       using TR = std::remove_pointer_t<decltype(R)>;
@@ -1184,6 +1220,14 @@ int cycle32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
   } else {
     ACHK(cycle32<M>(ctx, C, o, l + 1, MG_CYCLE_F, true, cfresh));
     ACHK(cycle32<M>(ctx, C, o, l + 1, MG_CYCLE_V, false));
+  }
+  if (mid) {
+    with_mid([&](const auto& P) {
+      k_mid_up<<<mid_blocks(Lf), kMidThreads, mid_up_lds(Lf), ctx->stream>>>(
+          Lf, Lc, P, W.ea[l], W.e[l + 1], W.e[l]);
+    });
+    LAUNCHCHK();
+    return MG_OK;
   }
   // f(R) only: the symmetron's closed form, inlined for each of the kernel's 16
   // cells, makes it slower than the two kernels (77 us against 15 + 30 at
@@ -1595,10 +1639,28 @@ int lin_cycle(mg_ctx* ctx, WorkLin<T>& W, double kap, const mg_solver_opts* o, i
     return MG_OK;
   }
   const Lev& Lc = ctx->L[l + 1];
-  smooth(o->nu_pre, fresh);
+  const bool mid = sizeof(T) == 4 && use_mid(ctx, o, l);
+  // a coarse level run in one launch takes its uncleared correction as zero
+  const bool cfresh = sizeof(T) == 4 && use_mid(ctx, o, l + 1);
+  auto with_mid = [&](auto&& fn) {
+    if constexpr (sizeof(T) == 4)
+      with_lin_store<T>(ctx, W, l, [&](auto* D, auto* R) {
+        using TD = std::remove_pointer_t<decltype(D)>;
+        using TR = std::remove_pointer_t<decltype(R)>;
+        fn(MidLin<TD, TR>{D, R, float(kh2), S0, vec ? 1 : 0});
+      });
+  };
+  if (!mid) smooth(o->nu_pre, fresh);
   const bool cvec = Lc.n % Vec<T>::V == 0;
   const int64_t ncv = cells(Lc) / Vec<T>::V;
-  if (o->nu_pre > 0 && Lc.n % 4 == 0 && Lc.n >= 8 &&  // exact per cell: colour 1 skipped
+  if (mid)
+    with_mid([&](const auto& P) {
+      k_mid_down<<<mid_blocks(Lf), kMidThreads, mid_down_lds(Lf), ctx->stream>>>(
+          Lf, Lc, P, (const float*)W.e[l], (float*)W.ea[l],
+          cfresh ? (float*)nullptr : (float*)W.e[l + 1], (float*)W.r[l + 1], (float*)nullptr,
+          (float*)nullptr, 0, fresh ? 1 : 0);
+    });
+  else if (o->nu_pre > 0 && Lc.n % 4 == 0 && Lc.n >= 8 &&  // exact per cell: colour 1 skipped
       prolong_march_blocks(Lc.n, kRestrictKT) >= ctx->march_min_blocks)
     with_lin_store<T>(ctx, W, l, [&](auto* D, auto* R) {
       using TD = std::remove_pointer_t<decltype(D)>;
@@ -1619,13 +1681,21 @@ int lin_cycle(mg_ctx* ctx, WorkLin<T>& W, double kap, const mg_solver_opts* o, i
         Lf, Lc, W.e[l], W.dg[l], W.r[l], kh2, W.r[l + 1], W.e[l + 1]);
   LAUNCHCHK();
   if (type == MG_CYCLE_V) {
-    ACHK(lin_cycle<T>(ctx, W, kap, o, l + 1, MG_CYCLE_V));
+    ACHK(lin_cycle<T>(ctx, W, kap, o, l + 1, MG_CYCLE_V, cfresh));
   } else if (type == MG_CYCLE_W) {
-    ACHK(lin_cycle<T>(ctx, W, kap, o, l + 1, MG_CYCLE_W));
+    ACHK(lin_cycle<T>(ctx, W, kap, o, l + 1, MG_CYCLE_W, cfresh));
     ACHK(lin_cycle<T>(ctx, W, kap, o, l + 1, MG_CYCLE_W));
   } else {
-    ACHK(lin_cycle<T>(ctx, W, kap, o, l + 1, MG_CYCLE_F));
+    ACHK(lin_cycle<T>(ctx, W, kap, o, l + 1, MG_CYCLE_F, cfresh));
     ACHK(lin_cycle<T>(ctx, W, kap, o, l + 1, MG_CYCLE_V));
+  }
+  if (mid) {
+    with_mid([&](const auto& P) {
+      k_mid_up<<<mid_blocks(Lf), kMidThreads, mid_up_lds(Lf), ctx->stream>>>(
+          Lf, Lc, P, (const float*)W.ea[l], (const float*)W.e[l + 1], (float*)W.e[l]);
+    });
+    LAUNCHCHK();
+    return MG_OK;
   }
   if constexpr (sizeof(T) == 4) {
     if (cvec && fuse_prolong(ctx, l)) {
@@ -2774,6 +2844,7 @@ size_t noalloc_layout(const mg_ctx* ctx, char* base, NoallocWork* W) {
     W->w32.rho[l] = (float*)take(4 * m);
     W->w32.dens[l] = (float*)take(4 * m);
     if (l > 0) W->w32.eR[l] = (float*)take(4 * m);
+    if (l < ctx->fused_from && ctx->L[l].n <= kMidMaxN) W->w32.ea[l] = (float*)take(2 * m);
     W->w64.v[l] = (double*)take(8 * m);
     if (l > 0) {
       W->w64.dens[l] = (double*)take(8 * m);
@@ -2841,6 +2912,7 @@ int mg_ctx_create(mg_ctx** out, int n, void* hip_stream) {
   }
   if (const char* pm = getenv("MGGPU_PROLONG_SMOOTH_MIN_BLOCKS"))
     ctx->psmooth_min_blocks = (unsigned)atoi(pm);
+  if (const char* mm = getenv("MGGPU_MID_MAX_N")) ctx->mid_max_n = std::min(atoi(mm), kMidMaxN);
   if (const char* sk = getenv("MGGPU_SMOOTH_MARCH_KT")) {
     const int kt = atoi(sk);
     ctx->smooth_march_kt = kt > 0 && kt <= 64 ? kt : 0;

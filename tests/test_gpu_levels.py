@@ -86,3 +86,30 @@ def test_small_levels_match_oracle(model, prec, n):
 def test_small_levels_second_visits_and_other_exponents(prec):
     solve_and_adjoint_match("sym", 32, prec, cycle="W")
     solve_and_adjoint_match("fr", 32, prec, cycle="F", fr_n=2)
+
+
+# one launch per way down and way up of a level against one per operation:
+# 8 and 12 (the tile's frame wraps the whole period), rows of 4 to 40 cells, 12
+# and 20 (rows of no multiple of 4), 96 and 160 (levels above the limit lead
+# into it), 16-bit and FP32 storage
+@pytest.mark.parametrize("model,n,cycle,fp16", [
+    ("fr", 8, "V", "1"), ("sym", 12, "V", "1"), ("fr", 20, "V", "1"), ("fr", 32, "W", "0"),
+    ("sym", 40, "F", "1"), ("fr", 56, "V", "0"), ("sym", 64, "W", "1"), ("fr", 80, "V", "1"),
+    ("fr", 96, "F", "1"), ("sym", 160, "V", "0")])
+def test_one_launch_levels_are_bit_identical(monkeypatch, model, n, cycle, fp16):
+    _, prm, delta = inputs(model, n, 91)
+    dt = torch.from_numpy(delta).to(DEV)
+    gv = torch.from_numpy(np.random.default_rng(92).standard_normal((n, n, n))).to(DEV)
+    monkeypatch.setenv("MGGPU_FP16_STORAGE", fp16)
+    got = []
+    for limit in ("0", "80"):
+        monkeypatch.setenv("MGGPU_MID_MAX_N", limit)
+        mg = api.Context(n, device=DEV)
+        o = api.solver_opts(cycle=cycle)
+        print("one-launch levels", model, n, cycle, fp16, limit, flush=True)
+        field, _ = mg.solve(model, prm, dt, tol=1e-6, opts=o)
+        gd, _ = mg.solve_adjoint(model, prm, dt, field, gv, tol=1e-6, opts=o)
+        got.append((field, gd))
+        mg.close()
+    assert torch.equal(got[0][0], got[1][0])
+    assert torch.equal(got[0][1], got[1][1])
