@@ -97,6 +97,10 @@ __device__ __forceinline__ float mul_nc(float a, float b) {
 #pragma clang fp contract(off)
   return a * b;
 }
+__device__ __forceinline__ double mul_nc(double a, double b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
 
 // Root of t^3 + p t + q = 0 on the branch the paper's closed forms select:
 // the single real root, else the largest of three (for q < 0: the unique

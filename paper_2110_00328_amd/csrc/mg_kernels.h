@@ -408,16 +408,12 @@ __global__ __launch_bounds__(kBlock) void k_unpack(Lev L, const TI* __restrict__
 // The same transposes on 8 natural cells of a row per thread (n % 8 == 0):
 // the row's even cells are 4 consecutive packed cells of one colour, its odd
 // cells 4 of the other.
+// v: the 8 natural values from cell 8 g8 on
 template <typename TI, typename TO>
-__global__ __launch_bounds__(kBlock) void k_pack8(Lev L, const TI* __restrict__ nat,
-                                                  TO* __restrict__ pk, double scale) {
-  const int64_t g8 = gid();
-  if (g8 >= 2 * L.half / 8) return;
-  const uint32_t g = (uint32_t)g8 * 8u;
+__device__ __forceinline__ void op_pack8(const Lev& L, const TI* v, TO* __restrict__ pk,
+                                         double scale, uint32_t g8) {
   int i0, j, k;
-  dec_nat(g, L, i0, j, k);
-  TI v[8];
-  ldn<TI, 8>(nat + g, v);
+  dec_nat(g8 * 8u, L, i0, j, k);
   TO ev[4], od[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -430,11 +426,18 @@ __global__ __launch_bounds__(kBlock) void k_pack8(Lev L, const TI* __restrict__ 
   stn<TO, 4>(pk + (uint32_t)(1 - p) * (uint32_t)L.half + row, od);
 }
 template <typename TI, typename TO>
-__global__ __launch_bounds__(kBlock) void k_unpack8(Lev L, const TI* __restrict__ pk,
-                                                    TO* __restrict__ nat, double scale) {
+__global__ __launch_bounds__(kBlock) void k_pack8(Lev L, const TI* __restrict__ nat,
+                                                  TO* __restrict__ pk, double scale) {
   const int64_t g8 = gid();
   if (g8 >= 2 * L.half / 8) return;
-  const uint32_t g = (uint32_t)g8 * 8u;
+  TI v[8];
+  ldn<TI, 8>(nat + g8 * 8, v);
+  op_pack8<TI, TO>(L, v, pk, scale, (uint32_t)g8);
+}
+template <typename TI, typename TO>
+__device__ __forceinline__ void op_unpack8(const Lev& L, const TI* __restrict__ pk,
+                                           TO* __restrict__ nat, double scale, uint32_t g8) {
+  const uint32_t g = g8 * 8u;
   int i0, j, k;
   dec_nat(g, L, i0, j, k);
   const int p = (j + k) & 1;
@@ -449,6 +452,12 @@ __global__ __launch_bounds__(kBlock) void k_unpack8(Lev L, const TI* __restrict_
     v[2 * q + 1] = TO(scale * double(od[q]));
   }
   stn<TO, 8>(nat + g, v);
+}
+template <typename TI, typename TO>
+__global__ __launch_bounds__(kBlock) void k_unpack8(Lev L, const TI* __restrict__ pk,
+                                                    TO* __restrict__ nat, double scale) {
+  const int64_t g8 = gid();
+  if (g8 < 2 * L.half / 8) op_unpack8<TI, TO>(L, pk, nat, scale, (uint32_t)g8);
 }
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_fill(T* __restrict__ p, int64_t m, T v) {
@@ -1168,22 +1177,16 @@ __device__ __forceinline__ void march_nbsum(const Lev& L, const double* __restri
     sum[q] = (xv[q] + xv[q + 1]) + (ym[q] + yp[q]) + (wo[0][q] + wo[2][q]);
 }
 
-template <int M, int N, typename TX = float, typename TR = float>
-__global__ __launch_bounds__(kBlock) void k_outer_fused_kv(Lev L, const double* __restrict__ w,
-                                                           const float* __restrict__ e,
-                                                           double* __restrict__ w_new,
-                                                           const float* __restrict__ dens,
-                                                           Consts C0, TR* __restrict__ rho,
-                                                           TX* __restrict__ X,
-                                                           float* __restrict__ e_zero,
-                                                           double* __restrict__ part,
-                                                           double* __restrict__ part_bg, int kt,
-                                                           Store S = Store{1, 1, 1, 1},
-                                                           double* __restrict__ part_max = nullptr) {
+// (every thread of the workgroup calls it; sh: 32 doubles of LDS)
+template <int M, typename TX, typename TR>
+__device__ __forceinline__ void op_outer_fused_kv(
+    const Lev& L, const double* __restrict__ w, const float* __restrict__ e,
+    double* __restrict__ w_new, const float* __restrict__ dens, const Consts& C,
+    TR* __restrict__ rho, TX* __restrict__ X, float* __restrict__ e_zero,
+    double* __restrict__ part, double* __restrict__ part_bg, int kt, Store S,
+    double* __restrict__ part_max, double* sh) {
   constexpr int V = kVOuter;
   static_assert(V == 4, "the stored 4-cell groups");
-  const Consts C = with_exponent<M, N>(C0);
-  __shared__ double sh[32];
   const MarchPos P = march_pos(L, kt, V);
   double acc = 0.0, accb = 0.0;  // sum d^2; sum (bg_coef delta)^2 when part_bg is given
   double amax = 0.0;             // max |d| when part_max is given
@@ -1245,6 +1248,22 @@ __global__ __launch_bounds__(kBlock) void k_outer_fused_kv(Lev L, const double* 
     const double tm = block_max(amax, sh);
     if (threadIdx.x == 0) part_max[blockIdx.x] = tm;
   }
+}
+template <int M, int N, typename TX = float, typename TR = float>
+__global__ __launch_bounds__(kBlock) void k_outer_fused_kv(Lev L, const double* __restrict__ w,
+                                                           const float* __restrict__ e,
+                                                           double* __restrict__ w_new,
+                                                           const float* __restrict__ dens,
+                                                           Consts C0, TR* __restrict__ rho,
+                                                           TX* __restrict__ X,
+                                                           float* __restrict__ e_zero,
+                                                           double* __restrict__ part,
+                                                           double* __restrict__ part_bg, int kt,
+                                                           Store S = Store{1, 1, 1, 1},
+                                                           double* __restrict__ part_max = nullptr) {
+  __shared__ double sh[32];
+  op_outer_fused_kv<M, TX, TR>(L, w, e, w_new, dens, with_exponent<M, N>(C0), rho, X, e_zero,
+                               part, part_bg, kt, S, part_max, sh);
 }
 
 // adjoint: lam_new = lam + e + shift, r = b - A lam_new, e_zero = 0;

@@ -181,12 +181,12 @@ struct mg_ctx {
   int bblock = 0, bvec = -1, bteam = -1;  // last tile shape used
   bool bpinned = false;                    // shape fixed by mg_batched_set_config
   std::string bkey;
-  // grouped level launches: per-box table, control words, block partials,
-  // per-box sums (device and pinned host)
+  // grouped level launches: per-box table, control words (device and pinned
+  // host), block partials, per-box sums (pinned host)
   GBox* gtab = nullptr;
   GCtl* gctl = nullptr;
+  GCtl* ghctl = nullptr;
   double* gpart = nullptr;
-  double* gsum = nullptr;
   double* ghsum = nullptr;
   int gcap = 0;
   int64_t gpart_cap = 0;
@@ -1981,9 +1981,9 @@ __global__ __launch_bounds__(kBlock) void k_force(Lev L, const double* __restric
 // registers (the field is read from HBM once); rows j +- 1 and the row's
 // edge cells come from L1/L2.  Requires n % 4 == 0.
 template <bool ADD>
-__global__ __launch_bounds__(kBlock) void k_force_kv(Lev L, const double* __restrict__ f,
-                                                     const double* __restrict__ pn, double sn,
-                                                     Consts C, float* __restrict__ out, int kt) {
+__device__ __forceinline__ void op_force_kv(const Lev& L, const double* __restrict__ f,
+                                            const double* __restrict__ pn, double sn,
+                                            const Consts& C, float* __restrict__ out, int kt) {
   constexpr int V = 4;
   const int n = L.n;
   const uint32_t ngrp = (uint32_t)n * (uint32_t)n / V;  // groups per plane
@@ -2041,6 +2041,17 @@ __global__ __launch_bounds__(kBlock) void k_force_kv(Lev L, const double* __rest
       win[1][q] = win[2][q];
     }
   }
+}
+template <bool ADD>
+__global__ __launch_bounds__(kBlock) void k_force_kv(Lev L, const double* __restrict__ f,
+                                                     const double* __restrict__ pn, double sn,
+                                                     Consts C, float* __restrict__ out, int kt) {
+  op_force_kv<ADD>(L, f, pn, sn, C, out, kt);
+}
+// and for the boxes of a class (box in blockIdx.y)
+__global__ __launch_bounds__(kBlock) void kg_force_kv(const GBox* __restrict__ tab, int kt) {
+  const GBox& B = tab[blockIdx.y];
+  if (B.force) op_force_kv<false>(B.L[0], B.field, nullptr, 0.0, B.C, B.force, kt);
 }
 // The same force on tiles of 64 x 16 cells of a plane (16 threads x 4 cells
 // per row, 16 rows), marching kt planes in z.  Plane k's values go through
@@ -2972,9 +2983,10 @@ void mg_ctx_destroy(mg_ctx* ctx) {
   if (ctx->bout) (void)hipFree(ctx->bout);
   for (void* p : {(void*)ctx->border, (void*)ctx->bteams, (void*)ctx->bwg, (void*)ctx->bctr,
                   (void*)ctx->bparts, (void*)ctx->babort, (void*)ctx->gtab, (void*)ctx->gctl,
-                  (void*)ctx->gpart, (void*)ctx->gsum})
+                  (void*)ctx->gpart})
     if (p) (void)hipFree(p);
   if (ctx->ghsum) (void)hipHostFree(ctx->ghsum);
+  if (ctx->ghctl) (void)hipHostFree(ctx->ghctl);
   for (int i = 0; i < mg_ctx::kGStreams; ++i) {
     if (ctx->gst[i]) (void)hipStreamDestroy(ctx->gst[i]);
     if (ctx->gjoin[i]) (void)hipEventDestroy(ctx->gjoin[i]);
@@ -3817,6 +3829,8 @@ int batch_launch_bs(mg_ctx* ctx, const std::vector<BoxDev>& host, int team_mode,
 // ---------------------------------------------------------------------------
 struct GClass {
   int n, model, nlev, f;
+  int march;         // outer step by marching, corrections start fresh
+  int mid;           // scratch for the one-launch levels is there
   int first, count;  // range of the class-ordered table
 };
 // 4 packed cells per thread on level l (its rows hold a multiple of 4)
@@ -3838,24 +3852,44 @@ int fused_level(const Lev* L, int nlev) {
   return f;
 }
 
+// levels that may run in one launch per way, and what they and the marching
+// outer step need beyond box_bytes
+bool g_mid_level(const mg_ctx* ctx, const GClass& K, const Lev* L, int l) {
+  return K.mid && K.model != MG_CQ && l < K.f && l + 1 < K.nlev && L[l].n <= ctx->mid_max_n;
+}
+size_t g_extra_bytes(const mg_ctx* ctx, const GClass& K, const Lev* L) {
+  auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  size_t t = K.march ? up(8 * (size_t)(2 * L[0].half)) : 0;
+  for (int l = 0; l < K.nlev; ++l)
+    if (g_mid_level(ctx, K, L, l)) t += up(4 * (size_t)L[l].half);
+  return t;
+}
+// planes per workgroup of a class's marching outer step
+int g_outer_kt(const GClass& K, const Lev& L0) {
+  return march_depth(L0.n, march_blocks(L0, L0.n, kVOuter) * (unsigned)K.count);
+}
+
 int g_grow(mg_ctx* ctx, int nb, int pstride) {
   if (nb > ctx->gcap || (int64_t)nb * pstride > ctx->gpart_cap) {
-    for (void** p : {(void**)&ctx->gtab, (void**)&ctx->gctl, (void**)&ctx->gpart,
-                     (void**)&ctx->gsum}) {
+    for (void** p : {(void**)&ctx->gtab, (void**)&ctx->gctl, (void**)&ctx->gpart}) {
       if (*p) (void)hipFree(*p);
       *p = nullptr;
     }
     if (ctx->ghsum) (void)hipHostFree(ctx->ghsum);
+    if (ctx->ghctl) (void)hipHostFree(ctx->ghctl);
     ctx->ghsum = nullptr;
+    ctx->ghctl = nullptr;
     ctx->gcap = 0;
     ctx->gpart_cap = 0;
     HIPCHK(hipMalloc((void**)&ctx->gtab, sizeof(GBox) * nb));
     HIPCHK(hipMalloc((void**)&ctx->gctl, sizeof(GCtl) * nb));
-    HIPCHK(hipMalloc((void**)&ctx->gpart, sizeof(double) * (size_t)nb * pstride));
-    HIPCHK(hipMalloc((void**)&ctx->gsum, sizeof(double) * nb));
+    // partials and sums of the residual, then of the background norm
+    HIPCHK(hipMalloc((void**)&ctx->gpart, sizeof(double) * 2 * (size_t)nb * pstride));
     void* h = nullptr;
-    HIPCHK(hipHostMalloc(&h, sizeof(double) * nb, hipHostMallocDefault));
+    HIPCHK(hipHostMalloc(&h, sizeof(double) * 2 * nb, hipHostMallocDefault));
     ctx->ghsum = (double*)h;
+    HIPCHK(hipHostMalloc(&h, sizeof(GCtl) * nb, hipHostMallocDefault));
+    ctx->ghctl = (GCtl*)h;
     ctx->gcap = nb;
     ctx->gpart_cap = (int64_t)nb * pstride;
   }
@@ -3885,7 +3919,7 @@ int g_join(mg_ctx* ctx, int ns) {
 
 template <int M>
 void g_smooth(mg_ctx* ctx, hipStream_t st, const GClass& K, const Lev& L, int it, int l,
-              int sweeps) {
+              int sweeps, bool fresh = false) {
   const GBox* tab = ctx->gtab + K.first;
   const GCtl* ctl = ctx->gctl + K.first;
   const bool vec = g_vec_rows(L);
@@ -3894,21 +3928,32 @@ void g_smooth(mg_ctx* ctx, hipStream_t st, const GClass& K, const Lev& L, int it
   if (vec && kt > 0 && march_blocks(L, kt, 4) * (unsigned)K.count >= ctx->march_min_blocks) {
     for (int s = 0; s < sweeps; ++s)
       for (int colour = 0; colour < 2; ++colour)
-        kg_smooth_kv<M><<<dim3(march_blocks(L, kt, 4), K.count), kBlock, 0, st>>>(tab, ctl, it, l,
-                                                                                 colour, kt);
+        kg_smooth_kv<M><<<dim3(march_blocks(L, kt, 4), K.count), kBlock, 0, st>>>(
+            tab, ctl, it, l, colour, kt, fresh && s == 0 ? 1 : 0);
     return;
   }
   const unsigned bx = vec ? nblk(L.half / 4) : nblk(L.half);
   for (int s = 0; s < sweeps; ++s)
     for (int colour = 0; colour < 2; ++colour)
-      kg_smooth<M><<<dim3(bx, K.count), kBlock, 0, st>>>(tab, ctl, it, l, colour,
-                                                                  vec ? 1 : 0);
+      kg_smooth<M><<<dim3(bx, K.count), kBlock, 0, st>>>(tab, ctl, it, l, colour, vec ? 1 : 0,
+                                                         vec && fresh && s == 0 ? 1 : 0);
+}
+
+// Level l of a class runs its way down and up in one launch each (use_mid of
+// a single box): up to kGMidTiles tiles in a launch; above, the tiles'
+// recomputation costs more than the launches they save (64 boxes of
+// 64^3-128^3: 10.5 ms without, 10.05 with 800, 11.4 with 3000; 12 of
+// 32^3-64^3: 2.8 / 2.2 / 2.25)
+constexpr unsigned kGMidTiles = 800;
+bool g_use_mid(const mg_ctx* ctx, const GClass& K, const Lev* L, const mg_solver_opts* o, int l) {
+  return g_mid_level(ctx, K, L, l) && o->nu_pre == 1 && o->nu_post == 1 && 
+         mid_blocks(L[l]) * (unsigned)K.count <= kGMidTiles;
 }
 
 // one cycle of a class from level l down (the recursion of cycle32)
 template <int M>
 int g_cycle(mg_ctx* ctx, hipStream_t st, const GClass& K, const Lev* L,
-            const mg_solver_opts* o, int it, int l, int type, bool rx) {
+            const mg_solver_opts* o, int it, int l, int type, bool rx, bool fresh) {
   const GBox* tab = ctx->gtab + K.first;
   const GCtl* ctl = ctx->gctl + K.first;
   if (l >= K.f) {
@@ -3933,29 +3978,46 @@ int g_cycle(mg_ctx* ctx, hipStream_t st, const GClass& K, const Lev* L,
   if (l == K.nlev - 1) {  // a grid that cannot be coarsened
     const int cap = o->coarse_sweeps > 0 ? o->coarse_sweeps : default_coarse_sweeps(L[0].n, 1);
     const int nu = o->nu_pre + o->nu_post;
-    g_smooth<M>(ctx, st, K, L[l], it, l, cap > nu ? cap : nu);
+    g_smooth<M>(ctx, st, K, L[l], it, l, cap > nu ? cap : nu, fresh);
     LAUNCHCHK();
     return MG_OK;
   }
   const Lev& Lc = L[l + 1];
-  g_smooth<M>(ctx, st, K, L[l], it, l, o->nu_pre);
+  const bool mid = g_use_mid(ctx, K, L, o, l);
+  if (!mid) g_smooth<M>(ctx, st, K, L[l], it, l, o->nu_pre, fresh);
   const int skip1 = (M != CQ && o->nu_pre > 0) ? 1 : 0;
   const bool rvec = g_vec_coarse(Lc) && g_vec_rows(L[l]);
   // shifted coarse form (as in cycle32): the coarse correction starts at
-  // zero, written by the restriction; the coarse level's linearisation
-  // point changes, so its first visit forms R X again
-  kg_down<M><<<dim3(rvec ? nblk(2 * Lc.half / 4) : nblk(2 * Lc.half), K.count), kBlock, 0,
-               st>>>(tab, ctl, it, l, rx ? 1 : 0, skip1, rvec ? 1 : 0);
+  // zero, written by the restriction or taken so by the level's first
+  // half-sweep (cfresh); the coarse level's linearisation point changes, so
+  // its first visit forms R X again
+  const bool cfresh = l + 1 < K.f && (g_vec_rows(Lc) || g_use_mid(ctx, K, L, o, l + 1)) &&
+                      (o->nu_pre > 0 || l + 1 == K.nlev - 1);
+  const int zero_e = cfresh ? 0 : 1;
+  const dim3 gmid(mid_blocks(L[l]), K.count);
+  if constexpr (M != CQ)
+    if (mid)
+      kg_mid_down<M><<<gmid, kMidThreads, mid_down_lds(L[l]), st>>>(
+          tab, ctl, it, l, rx ? 1 : 0, fresh ? 1 : 0, zero_e);
+  if (!mid)
+    kg_down<M><<<dim3(rvec ? nblk(2 * Lc.half / 4) : nblk(2 * Lc.half), K.count), kBlock, 0,
+                 st>>>(tab, ctl, it, l, rx ? 1 : 0, skip1, rvec ? 1 : 0, zero_e);
   LAUNCHCHK();
   if (type == MG_CYCLE_V) {
-    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_V, true));
+    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_V, true, cfresh));
   } else if (type == MG_CYCLE_W) {
-    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_W, true));
-    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_W, false));
+    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_W, true, cfresh));
+    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_W, false, false));
   } else {
-    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_F, true));
-    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_V, false));
+    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_F, true, cfresh));
+    ACHK(g_cycle<M>(ctx, st, K, L, o, it, l + 1, MG_CYCLE_V, false, false));
   }
+  if constexpr (M != CQ)
+    if (mid) {
+      kg_mid_up<M><<<gmid, kMidThreads, mid_up_lds(L[l]), st>>>(tab, ctl, it, l);
+      LAUNCHCHK();
+      return MG_OK;
+    }
   if (g_vec_coarse(Lc)) {
     kg_up<M == CQ ? 0 : 1><<<dim3(nblk(2 * Lc.half / 4), K.count), kBlock, 0, st>>>(
         tab, ctl, it, l);
@@ -3970,7 +4032,7 @@ int g_cycle(mg_ctx* ctx, hipStream_t st, const GClass& K, const Lev* L,
 template <int M>
 int g_class_cycle(mg_ctx* ctx, hipStream_t st, const GClass& K, const Lev* L,
                   const mg_solver_opts* o, int it) {
-  return g_cycle<M>(ctx, st, K, L, o, it, 0, o->cycle, it == 0);
+  return g_cycle<M>(ctx, st, K, L, o, it, 0, o->cycle, it == 0, K.march && it == 0);
 }
 
 // The whole batch: trial = one outer step of two cycles, no outputs (tuning).
@@ -4005,16 +4067,34 @@ int grouped_solve(mg_ctx* ctx, int nb, const mg_box_desc* boxes, const mg_solver
     K.count = (int)kv.second.size();
     for (int b : kv.second) order.push_back(b);
     for (int l = 0; l < kMaxLevB; ++l) levs.push_back(L[l]);
+    // marching outer step: whole vectors per row, and level 0's first
+    // half-sweep can take the uncleared correction as zero
+    K.march = g_vec_rows(L[0]) && o->nu_pre > 0 ? 1 : 0;
+    for (int b : kv.second) K.march = K.march && al16(boxes[b].delta, boxes[b].field) ? 1 : 0;
+    K.mid = 1;
     cls.push_back(K);
     total += (size_t)K.count * box_bytes(L, K.nlev);
     pstride = std::max(pstride, (int)nblk(2 * L[0].half));
+    if (K.march)
+      pstride = std::max(pstride, (int)march_blocks(L[0], g_outer_kt(K, L[0]), kVOuter));
   }
-  if (total > ctx->bpool_bytes) {
+  // the second master buffers and the one-launch levels' scratch (about a
+  // third more); left out, with the paths that use them, if memory is short
+  size_t extra = 0;
+  for (size_t c = 0; c < cls.size(); ++c)
+    extra += (size_t)cls[c].count * g_extra_bytes(ctx, cls[c], &levs[c * kMaxLevB]);
+  if (total + extra > ctx->bpool_bytes) {
     if (ctx->bpool) (void)hipFree(ctx->bpool);
     ctx->bpool = nullptr;
     ctx->bpool_bytes = 0;
-    HIPCHK(hipMalloc(&ctx->bpool, total));
-    ctx->bpool_bytes = total;
+    if (hipMalloc(&ctx->bpool, total + extra) != hipSuccess) {
+      (void)hipGetLastError();
+      ctx->bpool = nullptr;
+      for (GClass& K : cls) K.march = K.mid = 0;
+      extra = 0;
+      HIPCHK(hipMalloc(&ctx->bpool, total));
+    }
+    ctx->bpool_bytes = total + extra;
   }
   ACHK(g_grow(ctx, nb, pstride));
   const int ns = std::min((int)cls.size(), (int)mg_ctx::kGStreams);
@@ -4051,7 +4131,12 @@ int grouped_solve(mg_ctx* ctx, int nb, const mg_box_desc* boxes, const mg_solver
       B.delta = D.delta;
       B.field = D.field;
       B.force = trial ? nullptr : D.force;
-      B.w = (double*)take(8 * (size_t)(2 * L[0].half));
+      B.march = K.march;
+      B.nbg = K.march ? (int)nblk(2 * L[0].half / 8) : (int)nblk(2 * L[0].half);
+      B.nres = K.march ? (int)march_blocks(L[0], g_outer_kt(K, L[0]), kVOuter)
+                       : (int)nblk(2 * L[0].half);
+      B.w[0] = (double*)take(8 * (size_t)(2 * L[0].half));
+      if (K.march) B.w[1] = (double*)take(8 * (size_t)(2 * L[0].half));
       for (int l = 0; l < K.nlev; ++l) {
         const size_t bytes = 4 * (size_t)(2 * L[l].half);
         B.e[l] = (float*)take(bytes);
@@ -4059,6 +4144,7 @@ int grouped_solve(mg_ctx* ctx, int nb, const mg_box_desc* boxes, const mg_solver
         B.rho[l] = (float*)take(bytes);
         B.dens[l] = (float*)take(bytes);
         if (l > 0) B.eR[l] = (float*)take(bytes);
+        if (g_mid_level(ctx, K, L, l)) B.ea[l] = (float*)take(bytes / 2);
       }
       if (K.f < K.nlev) {
         B.F.nlev = K.nlev - K.f;
@@ -4077,77 +4163,87 @@ int grouped_solve(mg_ctx* ctx, int nb, const mg_box_desc* boxes, const mg_solver
   }
   HIPCHK(hipMemcpyAsync(ctx->gtab, host.data(), sizeof(GBox) * nb, hipMemcpyHostToDevice,
                         ctx->stream));
-  // inputs packed, density pyramids, background norms
-  ACHK(g_fork(ctx, ns));
-  for (size_t c = 0; c < cls.size(); ++c) {
-    const GClass& K = cls[c];
-    const Lev* L = &levs[c * kMaxLevB];
-    const GBox* tab = ctx->gtab + K.first;
-    double* part = ctx->gpart + (int64_t)K.first * pstride;
-    const dim3 g0(nblk(2 * L[0].half), K.count);
-    hipStream_t st = cst(c);
-    if (K.model == MG_FR) kg_pack<FR><<<g0, kBlock, 0, st>>>(tab, part, pstride);
-    else if (K.model == MG_SYMMETRON) kg_pack<SYM><<<g0, kBlock, 0, st>>>(tab, part, pstride);
-    else kg_pack<CQ><<<g0, kBlock, 0, st>>>(tab, part, pstride);
-    if (K.model != MG_FR)
-      for (int l = 0; l + 1 < K.nlev; ++l)
-        kg_restrict_dens<<<dim3(nblk(2 * L[l + 1].half), K.count), kBlock, 0, st>>>(tab, l);
+  // the control words of the next launches, in the pinned buffer (the previous
+  // ones have been read: the host has waited for the sums since)
+  GCtl* ctl = ctx->ghctl;
+  auto put_ctl = [&]() -> int {
+    kg_ctl<<<1, kBlock, 0, ctx->stream>>>(ctl, ctx->gctl, nb);
     LAUNCHCHK();
-  }
-  // per-box sums of the partials (class streams), then joined and copied out
-  auto box_sums = [&](std::vector<double>& s) -> int {
+    return MG_OK;
+  };
+  // fn(class, levels, stream, model constant) for each class
+  auto each = [&](auto&& fn) -> int {
     for (size_t c = 0; c < cls.size(); ++c) {
       const GClass& K = cls[c];
       const Lev* L = &levs[c * kMaxLevB];
-      kg_sum_box<<<K.count, 256, 0, cst(c)>>>(ctx->gpart + (int64_t)K.first * pstride, pstride,
-                                               (int)nblk(2 * L[0].half), ctx->gsum + K.first);
+      if (K.model == MG_FR) ACHK(fn(K, L, cst(c), std::integral_constant<int, FR>()));
+      else if (K.model == MG_SYMMETRON) ACHK(fn(K, L, cst(c), std::integral_constant<int, SYM>()));
+      else ACHK(fn(K, L, cst(c), std::integral_constant<int, CQ>()));
     }
     LAUNCHCHK();
-    ACHK(g_join(ctx, ns));
-    HIPCHK(hipMemcpyAsync(ctx->ghsum, ctx->gsum, sizeof(double) * nb, hipMemcpyDeviceToHost,
-                          ctx->stream));
-    HIPCHK(hipStreamSynchronize(ctx->stream));
-    s.assign(ctx->ghsum, ctx->ghsum + nb);
     return MG_OK;
   };
-  std::vector<double> sums;
-  ACHK(box_sums(sums));
+  // w += e and the residual at w, on the class streams
+  auto outer_pass = [&]() -> int {
+    return each([&](const GClass& K, const Lev* L, hipStream_t st, auto M) -> int {
+      const GBox* tab = ctx->gtab + K.first;
+      const GCtl* gc = ctx->gctl + K.first;
+      double* part = ctx->gpart + (int64_t)K.first * pstride;
+      if (K.march) {
+        const int kt = g_outer_kt(K, L[0]);
+        kg_outer_march<M><<<dim3(march_blocks(L[0], kt, kVOuter), K.count), kBlock, 0, st>>>(
+            tab, gc, part, pstride, kt);
+        return MG_OK;
+      }
+      const dim3 g0(nblk(2 * L[0].half), K.count);
+      kg_update<<<g0, kBlock, 0, st>>>(tab, gc);
+      kg_outer<M><<<g0, kBlock, 0, st>>>(tab, gc, part, pstride);
+      return MG_OK;
+    });
+  };
+  // sums of the partials, joined, to the host
+  auto box_sums = [&](bool bg) -> int {
+    ACHK(g_join(ctx, ns));
+    kg_sum_box<<<dim3(nb, bg ? 2 : 1), 256, 0, ctx->stream>>>(ctx->gtab, ctx->gpart, pstride,
+                                                              ctx->ghsum);
+    LAUNCHCHK();
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    return MG_OK;
+  };
+  // inputs packed, density pyramids, background norms, first residuals
+  for (int i = 0; i < nb; ++i) ctl[i] = GCtl{1, 0, 0, 0};
+  ACHK(put_ctl());
+  ACHK(g_fork(ctx, ns));
+  ACHK(each([&](const GClass& K, const Lev* L, hipStream_t st, auto M) -> int {
+    const GBox* tab = ctx->gtab + K.first;
+    double* part = ctx->gpart + (int64_t)(nb + K.first) * pstride;
+    if (K.march)
+      kg_pack8<M><<<dim3(nblk(2 * L[0].half / 8), K.count), kBlock, 0, st>>>(tab, part, pstride);
+    else
+      kg_pack<M><<<dim3(nblk(2 * L[0].half), K.count), kBlock, 0, st>>>(tab, part, pstride);
+    if (K.model != MG_FR)
+      for (int l = 0; l + 1 < K.nlev; ++l)
+        kg_restrict_dens<<<dim3(nblk(2 * L[l + 1].half), K.count), kBlock, 0, st>>>(tab, l);
+    return MG_OK;
+  }));
+  ACHK(outer_pass());
+  ACHK(box_sums(true));
   std::vector<double> eps(nb), rel(nb, 0.0), rel_prev(nb, -1.0), mcell(nb);
   std::vector<int> k_prev(nb, 0), outer(nb, 0), vc(nb, 0), status(nb, 0), done(nb, 0);
   for (int i = 0; i < nb; ++i) {
     const GBox& B = host[i];
     mcell[i] = 2.0 * double(B.L[0].half);
-    eps[i] = bg_norm_of(B.C, sqrt(sums[i] / mcell[i]));
+    eps[i] = bg_norm_of(B.C, sqrt(ctx->ghsum[nb + i] / mcell[i]));
   }
   const int max_outer = trial ? 1 : o->max_cycles;
-  std::vector<GCtl> ctl(nb);
-  for (int i = 0; i < nb; ++i) ctl[i] = GCtl{1, 0, 0, 0};
   for (;;) {
-    HIPCHK(hipMemcpyAsync(ctx->gctl, ctl.data(), sizeof(GCtl) * nb, hipMemcpyHostToDevice,
-                          ctx->stream));
-    ACHK(g_fork(ctx, ns));
-    for (size_t c = 0; c < cls.size(); ++c) {
-      const GClass& K = cls[c];
-      const Lev* L = &levs[c * kMaxLevB];
-      const GBox* tab = ctx->gtab + K.first;
-      const GCtl* gc = ctx->gctl + K.first;
-      double* part = ctx->gpart + (int64_t)K.first * pstride;
-      const dim3 g0(nblk(2 * L[0].half), K.count);
-      hipStream_t st = cst(c);
-      kg_update<<<g0, kBlock, 0, st>>>(tab, gc);
-      if (K.model == MG_FR) kg_outer<FR><<<g0, kBlock, 0, st>>>(tab, gc, part, pstride);
-      else if (K.model == MG_SYMMETRON) kg_outer<SYM><<<g0, kBlock, 0, st>>>(tab, gc, part, pstride);
-      else kg_outer<CQ><<<g0, kBlock, 0, st>>>(tab, gc, part, pstride);
-    }
-    LAUNCHCHK();
-    ACHK(box_sums(sums));
     int kmax = 0;
     for (int i = 0; i < nb; ++i) {
       if (done[i]) {
-        ctl[i] = GCtl{0, 0, 0, 0};
+        ctl[i] = GCtl{0, 0, 0, outer[i]};
         continue;
       }
-      rel[i] = sqrt(sums[i] / mcell[i]) / eps[i];
+      rel[i] = sqrt(ctx->ghsum[i] / mcell[i]) / eps[i];
       int kb = 0;
       if (!std::isfinite(rel[i])) {
         status[i] = MG_ENAN;
@@ -4162,52 +4258,51 @@ int grouped_solve(mg_ctx* ctx, int nb, const mg_box_desc* boxes, const mg_solver
                    : plan_cycles(o->inner_cycles, rel[i], rel_prev[i], k_prev[i], tol,
                                  (int64_t)mcell[i]);
       }
-      ctl[i] = GCtl{kb > 0 ? 1 : 0, kb, kb > 0 ? 1 : 0, 0};
       if (kb > 0) {
         vc[i] += kb;
         rel_prev[i] = rel[i];
         k_prev[i] = kb;
         ++outer[i];
       }
+      ctl[i] = GCtl{kb > 0 ? 1 : 0, kb, kb > 0 ? 1 : 0, outer[i]};
       kmax = std::max(kmax, kb);
     }
+    ACHK(put_ctl());
+    ACHK(g_fork(ctx, ns));
     if (kmax == 0) break;
-    HIPCHK(hipMemcpyAsync(ctx->gctl, ctl.data(), sizeof(GCtl) * nb, hipMemcpyHostToDevice,
-                          ctx->stream));
-    ACHK(g_fork(ctx, ns));
     for (int it = 0; it < kmax; ++it)
-      for (size_t c = 0; c < cls.size(); ++c) {
-        const GClass& K = cls[c];
-        const Lev* L = &levs[c * kMaxLevB];
-        hipStream_t st = cst(c);
-        if (K.model == MG_FR) ACHK(g_class_cycle<FR>(ctx, st, K, L, o, it));
-        else if (K.model == MG_SYMMETRON) ACHK(g_class_cycle<SYM>(ctx, st, K, L, o, it));
-        else ACHK(g_class_cycle<CQ>(ctx, st, K, L, o, it));
-      }
-    ACHK(g_join(ctx, ns));  // before the control words are rewritten
+      ACHK(each([&](const GClass& K, const Lev* L, hipStream_t st, auto M) -> int {
+        return g_class_cycle<M>(ctx, st, K, L, o, it);
+      }));
+    ACHK(outer_pass());
+    ACHK(box_sums(false));
   }
-  if (!trial) {
-    ACHK(g_fork(ctx, ns));
-    for (size_t c = 0; c < cls.size(); ++c) {
-      const GClass& K = cls[c];
-      const Lev* L = &levs[c * kMaxLevB];
+  if (!trial)
+    ACHK(each([&](const GClass& K, const Lev* L, hipStream_t st, auto M) -> int {
       const GBox* tab = ctx->gtab + K.first;
       const dim3 g0(nblk(2 * L[0].half), K.count);
-      hipStream_t st = cst(c);
-      if (K.model == MG_FR) {
-        kg_unpack<FR><<<g0, kBlock, 0, st>>>(tab);
-        kg_force<FR><<<g0, kBlock, 0, st>>>(tab);
-      } else if (K.model == MG_SYMMETRON) {
-        kg_unpack<SYM><<<g0, kBlock, 0, st>>>(tab);
-        kg_force<SYM><<<g0, kBlock, 0, st>>>(tab);
-      } else {
-        kg_unpack<CQ><<<g0, kBlock, 0, st>>>(tab);
-        kg_force<CQ><<<g0, kBlock, 0, st>>>(tab);
+      if (K.march)
+        kg_unpack8<M><<<dim3(nblk(2 * L[0].half / 8), K.count), kBlock, 0, st>>>(
+            tab, ctx->gctl + K.first);
+      else
+        kg_unpack<M><<<g0, kBlock, 0, st>>>(tab);
+      bool any = false, al = L[0].n % 4 == 0;
+      for (int q = 0; q < K.count; ++q) {
+        const GBox& B = host[K.first + q];
+        any = any || B.force;
+        al = al && al16(B.field, B.force);
       }
-    }
-    LAUNCHCHK();
-    ACHK(g_join(ctx, ns));
-  }
+      if (any && al) {
+        unsigned nchunk = (unsigned)(((int64_t)K.n * K.n / 4 + kBlock - 1) / kBlock);
+        const int kt = march_depth(K.n, nchunk * (unsigned)K.count);
+        kg_force_kv<<<dim3(nchunk * (unsigned)((K.n + kt - 1) / kt), K.count), kBlock, 0, st>>>(
+            tab, kt);
+      } else if (any) {
+        kg_force<M><<<g0, kBlock, 0, st>>>(tab);
+      }
+      return MG_OK;
+    }));
+  ACHK(g_join(ctx, ns));
   // the host table must outlive its asynchronous upload
   HIPCHK(hipStreamSynchronize(ctx->stream));
   outs.assign(nb, BoxOut());

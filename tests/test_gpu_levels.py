@@ -113,3 +113,51 @@ def test_one_launch_levels_are_bit_identical(monkeypatch, model, n, cycle, fp16)
         mg.close()
     assert torch.equal(got[0][0], got[1][0])
     assert torch.equal(got[0][1], got[1][1])
+
+
+# boxes solved together: the marching outer step with two master buffers (rows
+# of a multiple of 8 cells, aligned arrays) against the separate kernels, which
+# arrays at odd addresses take; one-launch levels bit for bit against separate
+# ones.  From the background, from a given field, stopped at once (the field is
+# then the start) and with two sweeps (no one-launch levels).
+@pytest.mark.parametrize("sizes,cycle,nu,start,tol", [
+    ((8, 16, 8), "V", 1, False, 1e-8), ((12, 24), "V", 1, False, 1e-8),
+    ((32, 48, 64), "V", 1, True, 1e-8), ((32, 40), "F", 1, False, 1e-8),
+    ((64, 64, 96), "W", 2, False, 1e-8), ((16, 72), "V", 1, False, 1e30),
+    ((24, 32), "V", 1, True, 1e30)])
+def test_boxes_together_take_the_same_steps(monkeypatch, sizes, cycle, nu, start, tol):
+    got = []
+    for limit, off in (("80", 0), ("0", 0), ("80", 1)):
+        monkeypatch.setenv("MGGPU_MID_MAX_N", limit)
+        mg = api.Context(8, device=DEV)
+        mg.batched_set_config(256, 1, 2)
+        boxes = []
+        for q, n in enumerate(n for n in sizes for _ in range(2)):
+            model = ("fr", "sym")[q % 2]
+            P, prm, d = inputs(model, n, 300 + q)
+            m = n ** 3
+            bg = (-1.0 if model == "fr" else 1.0) * oracle.background(P)
+            field = torch.full((m + 1,), 1.25 * bg, dtype=torch.float64, device=DEV)[off:off + m]
+            delta = torch.zeros(m + 1, dtype=torch.float32, device=DEV)[off:off + m]
+            delta.copy_(torch.from_numpy(d.ravel()))
+            force = torch.zeros(3 * m + 1, dtype=torch.float32, device=DEV)[off:off + 3 * m]
+            boxes.append(dict(n=n, model=model, params=prm, delta=delta.view(n, n, n),
+                              field=field.view(n, n, n), force=force.view(3, n, n, n),
+                              field_in=1 if start else 0, bg=bg))
+        print("boxes together", sizes, cycle, nu, start, limit, off, flush=True)
+        st = mg.solve_batched(boxes, tol=tol,
+                              opts=api.solver_opts(cycle=cycle, nu_pre=nu, nu_post=nu))
+        assert all(s.status == 0 and s.rel_resid <= tol for s in st)
+        got.append([(b["field"].cpu().numpy(), b["force"].cpu().numpy(), b["bg"]) for b in boxes])
+        mg.close()
+    for one, sep, plain in zip(*got):
+        assert np.array_equal(one[0], sep[0]) and np.array_equal(one[1], sep[1])
+        if tol > 1:
+            if start:
+                assert np.all(one[0] == 1.25 * one[2])
+            assert np.allclose(one[0], (1.25 if start else 1.0) * one[2], rtol=1e-13, atol=0.0)
+            assert np.array_equal(one[0], plain[0])
+            assert not one[1].any() and not plain[1].any()
+            continue
+        for a, b, ref in zip(one[:2], plain[:2], (one[2], 0.0)):
+            assert np.linalg.norm(a - b) <= 1e-6 * np.linalg.norm(b - ref)
