@@ -128,7 +128,8 @@ typedef struct mg_ctx mg_ctx;
  * FP32-refined solve in FP32 instead of 16-bit floats (default 1; n % 8 == 0
  * grids; changes rounding inside the FP32 correction cycles only, the FP64
  * residual and the solution's tolerance are unaffected).  MGGPU_CIC_DIRECT=1
- * makes cic_assign always take its direct atomic path (identical results).
+ * makes cic_assign always take its direct atomic path, 0 its binned path
+ * (identical results; by default the faster one for the particles and cells).
  * Returns MG_EINVAL for a bad n or NULL out. */
 int mg_ctx_create(mg_ctx **out, int n, void *hip_stream);
 void mg_ctx_destroy(mg_ctx *ctx);

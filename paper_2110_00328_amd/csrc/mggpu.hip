@@ -163,7 +163,8 @@ struct mg_ctx {
   unsigned long long* cic_runs = nullptr;  // runs in (tile, class) bin order
   int64_t cic_np = 0;
   uint32_t* cic_cnt = nullptr;  // counts, offsets, cursors per (tile, class) bin
-  int cic_direct = 0;           // 1: always the direct atomic path (MGGPU_CIC_DIRECT)
+  int cic_direct = -1;          // 1: always the direct atomic path, 0: always binned
+                                // (MGGPU_CIC_DIRECT; else by cic_binned)
   // batched solves
   void* bpool = nullptr;
   size_t bpool_bytes = 0;
@@ -2342,7 +2343,7 @@ __global__ __launch_bounds__(kBlock) void k_cic_finish(int64_t m, const unsigned
   if (g < m) delta[g] = float(double(acc[g]) * scale - 1.0);
 }
 
-// ---- binned CIC: tiles of kT^3 cells ------------------------------------
+// ---- binned CIC: tiles of kT^3 cells (the last along an axis may be thinner)
 // Particles are sorted by bin = (tile, class).  Bit a of the class is set when
 // the particle's lower cell is the last layer of its tile along axis a, so
 // that the particle also reaches the next tile along a.  The workgroup of a
@@ -2352,11 +2353,13 @@ __global__ __launch_bounds__(kBlock) void k_cic_finish(int64_t m, const unsigned
 constexpr int kT = 16;  // tile edge (cells)
 constexpr int kT3 = kT * kT * kT;
 
-__device__ __forceinline__ uint32_t bin_of(const CicCell& c, int nt) {
+__device__ __forceinline__ uint32_t bin_of(const CicCell& c, int n, int nt) {
   const uint32_t t =
       ((uint32_t)(c.i0[2] / kT) * nt + (uint32_t)(c.i0[1] / kT)) * nt + (uint32_t)(c.i0[0] / kT);
-  const uint32_t cls = (c.i0[0] % kT == kT - 1 ? 1u : 0u) | (c.i0[1] % kT == kT - 1 ? 2u : 0u) |
-                       (c.i0[2] % kT == kT - 1 ? 4u : 0u);
+  uint32_t cls = 0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    cls |= c.i0[a] % kT == kT - 1 || c.i0[a] == n - 1 ? 1u << a : 0u;
   return 8u * t + cls;
 }
 
@@ -2382,14 +2385,16 @@ __device__ __forceinline__ CicRun cic_run(uint32_t t, bool valid) {
   return r;
 }
 
-// The count and placement passes take a region of kCicRegion consecutive
-// particles per workgroup, kCicRounds rounds of kCicPer groups of kCicCB
-// consecutive particles (a wave's 64 lanes hold 64 consecutive particles);
-// all loads of a round are issued before their results are used.
+// The count and placement passes take a region of consecutive particles per
+// workgroup, up to kCicRounds rounds of kCicPer groups of kCicCB consecutive
+// particles (a wave's 64 lanes hold 64 consecutive particles); all loads of a
+// round are issued before their results are used.  Long regions share more
+// atomics on the bins' counters; fewer rounds are taken where the regions
+// would not fill the chip (cic_rounds).
 constexpr int kCicCB = 512;    // workgroup size of the count and placement passes
 constexpr int kCicPer = 4;
 constexpr int kCicRounds = 4;
-constexpr int kCicRegion = kCicCB * kCicPer * kCicRounds;  // particles (and at most runs)
+constexpr int kCicRound = kCicCB * kCicPer;       // particles (and at most runs) per round
 constexpr int kCicBinBits = 26;  // run record: bin | (length - 1) << 26
 // Per-workgroup LDS table bin -> count (open addressing, linear probing):
 // the global counters and cursors take one atomic per distinct bin of a
@@ -2440,7 +2445,7 @@ __device__ __forceinline__ void cic_chunk(int n, int nt, int64_t np, const float
   }
 #pragma unroll
   for (int q = 0; q < kCicPer; ++q)
-    c.bin[q] = c.valid[q] ? bin_of(cic_cell(n, c.x[q], 0), nt) : 0xffffffffu;
+    c.bin[q] = c.valid[q] ? bin_of(cic_cell(n, c.x[q], 0), n, nt) : 0xffffffffu;
 }
 
 // Count pass: each run of equal bins becomes one record {first particle,
@@ -2453,7 +2458,7 @@ __device__ __forceinline__ void cic_chunk(int n, int nt, int64_t np, const float
 __global__ __launch_bounds__(kCicCB) void k_cic_runs(int n, int nt, int64_t np,
                                                      const float* __restrict__ pos, uint32_t* cnt,
                                                      uint2* __restrict__ rec,
-                                                     uint32_t* __restrict__ nrec) {
+                                                     uint32_t* __restrict__ nrec, int rounds) {
   constexpr int kW = kCicCB / 64;
   __shared__ uint32_t key[kCicH], val[kCicH];
   __shared__ uint32_t wcount[kCicPer * kW], woff[kCicPer * kW];
@@ -2464,10 +2469,11 @@ __global__ __launch_bounds__(kCicCB) void k_cic_runs(int n, int nt, int64_t np,
   }
   __syncthreads();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint2* R = rec + (int64_t)blockIdx.x * kCicRegion;
+  const int64_t region = (int64_t)kCicRound * rounds;
+  uint2* R = rec + blockIdx.x * region;
   uint32_t rbase = 0;  // records written by the earlier rounds (same on every thread)
-  for (int round = 0; round < kCicRounds; ++round) {
-    const int64_t first = (int64_t)blockIdx.x * kCicRegion + (int64_t)round * kCicCB * kCicPer;
+  for (int round = 0; round < rounds; ++round) {
+    const int64_t first = blockIdx.x * region + (int64_t)round * kCicRound;
     CicChunk c;
     cic_chunk(n, nt, np, pos, first, c);
     CicRun r[kCicPer];
@@ -2565,7 +2571,8 @@ __global__ __launch_bounds__(1024) void k_cic_scan(const uint32_t* __restrict__ 
 __global__ __launch_bounds__(kCicCB) void k_cic_place(const uint2* __restrict__ rec,
                                                       const uint32_t* __restrict__ nrec,
                                                       uint32_t* cur,
-                                                      unsigned long long* __restrict__ runs) {
+                                                      unsigned long long* __restrict__ runs,
+                                                      int rounds) {
   __shared__ uint32_t key[kCicH], val[kCicH], base[kCicH];
   for (int h = threadIdx.x; h < kCicH; h += kCicCB) {
     key[h] = kCicEmpty;
@@ -2573,7 +2580,7 @@ __global__ __launch_bounds__(kCicCB) void k_cic_place(const uint2* __restrict__ 
   }
   __syncthreads();
   const uint32_t nr = nrec[blockIdx.x];
-  const uint2* R = rec + (int64_t)blockIdx.x * kCicRegion;
+  const uint2* R = rec + (int64_t)blockIdx.x * kCicRound * rounds;
   for (uint32_t i = threadIdx.x; i < nr; i += kCicCB) {
     const int h = cic_insert(key, R[i].y & ((1u << kCicBinBits) - 1u));
     if (h >= 0) atomicAdd(&val[h], 1u);
@@ -2596,8 +2603,8 @@ __global__ __launch_bounds__(kCicCB) void k_cic_place(const uint2* __restrict__ 
 // One workgroup per tile.  Segments: the tile's own 8 bins (one contiguous
 // range of runs, role 0) and, for each lower neighbour at offset -s (s a
 // non-empty subset of the axes, role s), its bins whose class contains s.
-// In role s a particle's local coordinate on axis a is its in-tile layer
-// minus kT s_a, and only corners that land inside the tile are added: each
+// In role s a particle's local coordinate on axis a is its in-tile layer, or
+// -1 where s_a is set, and only corners that land inside the tile are added: each
 // corner of each particle lands in exactly one (tile, role).  Runs are taken
 // in batches of at most kCicTB runs and kCicCap particles: their lengths
 // are prefix-summed, the batch's particles numbered consecutively, and a
@@ -2612,6 +2619,9 @@ constexpr int kCicUnroll = 2;  // particles per thread in flight
 constexpr int kCicTB = 512;    // workgroup size of the tile kernel
 constexpr int kCicWords = kCicTB;          // bitmap words, one per thread
 constexpr int kCicCap = 32 * kCicWords;    // particles per batch (a run is at most 64)
+// FULL: the side is a multiple of kT, every tile has kT^3 cells (187 against 207
+// us at 256^3 particles with the edges in registers)
+template <bool FULL>
 __global__ __launch_bounds__(kCicTB) void k_cic_tile(int n, int nt, const float* __restrict__ pos,
                                                      const unsigned long long* __restrict__ runs,
                                                      const uint32_t* __restrict__ boff,
@@ -2633,6 +2643,9 @@ __global__ __launch_bounds__(kCicTB) void k_cic_tile(int n, int nt, const float*
   uint32_t t = blockIdx.x;
   if (ntiles % 8 == 0) t = (t & 7u) * (ntiles / 8) + (t >> 3);
   const int ti = (int)(t % nt), tj = (int)((t / nt) % nt), tk = (int)(t / ((uint32_t)nt * nt));
+  // the tile's edges
+  const int ei = FULL ? kT : min(kT, n - ti * kT), ej = FULL ? kT : min(kT, n - tj * kT),
+            ek = FULL ? kT : min(kT, n - tk * kT);
   for (int q = threadIdx.x; q < kT3; q += kCicTB) acc[q] = 0ull;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (threadIdx.x < 64) {
@@ -2761,13 +2774,13 @@ __global__ __launch_bounds__(kCicTB) void k_cic_tile(int n, int nt, const float*
         const int s = rl[u];
         long long w[8];
         cic_weights(cc[u], w);
-        // local lower corner in [-1, kT - 1] per axis (-1: the lower
+        // local lower corner in [-1, edge - 1] per axis (-1: the lower
         // neighbour's last layer, role bit set)
-        const int a = (cc[u].i0[0] & (kT - 1)) - ((s & 1) ? kT : 0);
-        const int b = (cc[u].i0[1] & (kT - 1)) - ((s & 2) ? kT : 0);
-        const int d = (cc[u].i0[2] & (kT - 1)) - ((s & 4) ? kT : 0);
-        const bool ox[2] = {a >= 0, a < kT - 1}, oy[2] = {b >= 0, b < kT - 1},
-                   oz[2] = {d >= 0, d < kT - 1};
+        const int a = (s & 1) ? -1 : cc[u].i0[0] & (kT - 1);
+        const int b = (s & 2) ? -1 : cc[u].i0[1] & (kT - 1);
+        const int d = (s & 4) ? -1 : cc[u].i0[2] & (kT - 1);
+        const bool ox[2] = {a >= 0, a < ei - 1}, oy[2] = {b >= 0, b < ej - 1},
+                   oz[2] = {d >= 0, d < ek - 1};
         const int c0 = (d * kT + b) * kT + a;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -2782,6 +2795,7 @@ __global__ __launch_bounds__(kCicTB) void k_cic_tile(int n, int nt, const float*
   }
   for (int q = threadIdx.x; q < kT3; q += kCicTB) {
     const int x = q % kT, y = (q / kT) % kT, z = q / (kT * kT);
+    if (x >= ei || y >= ej || z >= ek) continue;
     const int64_t cell = ((int64_t)(tk * kT + z) * n + (tj * kT + y)) * n + (ti * kT + x);
     delta[cell] = float(double(acc[q]) * scale - 1.0);
   }
@@ -2914,7 +2928,7 @@ int mg_ctx_create(mg_ctx** out, int n, void* hip_stream) {
   mg_ctx* ctx = new mg_ctx();
   ctx->n = n;
   if (const char* mb = getenv("MGGPU_MARCH_MIN_BLOCKS")) ctx->march_min_blocks = (unsigned)atoi(mb);
-  if (const char* cd = getenv("MGGPU_CIC_DIRECT")) ctx->cic_direct = atoi(cd) != 0;
+  if (const char* cd = getenv("MGGPU_CIC_DIRECT")) ctx->cic_direct = atoi(cd) != 0 ? 1 : 0;
   if (const char* ts = getenv("MGGPU_TEST_CORRECTION_SCALE")) ctx->test_escale = (float)atof(ts);
   if (const char* fs = getenv("MGGPU_FP16_STORAGE")) ctx->fp16 = atoi(fs) != 0;
   if (const char* pk = getenv("MGGPU_PROLONG_SMOOTH_KT")) {
@@ -3010,35 +3024,92 @@ const char* mg_last_error(const mg_ctx* ctx) { return ctx ? ctx->err.c_str() : "
 
 int mg_ctx_levels(const mg_ctx* ctx) { return ctx ? ctx->nlev : 0; }
 
+// Whether np particles are binned by tiles rather than deposited with global
+// atomics.  Those take 0.25 (grid order) to 0.35 ns (no order) a particle and
+// little else (8^3 to 32^3 cells: 13-20 us in all); the binned path takes five
+// dependent launches (35 us) and then 4.4 ns a particle in each tile, tiles in
+// parallel, so it needs many tiles and many particles.  Binned / direct, us:
+// 64^3 cells 51 / 70 at 64^3 particles, 36 / 17 at 32^3; 100^3 cells 30 / 47 at
+// 50^3, 70 / 262 at 100^3; 200^3 cells, no order, 100^3 particles 163 / 373;
+// 32^3 cells (8 tiles) 157 / 67 at 64^3.  27 full tiles (48^3) repay it from 8
+// particles a cell on (182 / 217); thinner last tiles leave the others more.
+bool cic_binned(const mg_ctx* ctx, int64_t np, int64_t ntiles) {
+  if (ctx->cic_direct == 1 || np >= (int64_t)0xffffffffLL - kCicRound * kCicRounds ||
+      8 * ntiles >= ((int64_t)1 << kCicBinBits))
+    return false;
+  if (ctx->cic_direct == 0) return true;
+  return (ntiles >= 64 && np >= (1 << 17)) ||
+         (ntiles >= 27 && ctx->n % kT == 0 && np >= (1 << 19));
+}
+
+// Rounds per region of the binned path: all of them where a tile holds many
+// particles, whose regions would otherwise queue at the same counters (in no
+// order, us with 4 rounds / fewer: 100^3 cells and particles 146 / 188, 128^3
+// 191 / 222); else the most that leave two regions per CU (50^3 particles in
+// 100^3 cells 42 / 30 in grid order, 56 / 41 in none; 128^3 in 256^3 107 / 91).
+int cic_rounds(int64_t np, int64_t ntiles) {
+  int r = kCicRounds;
+  if (np >= 1024 * ntiles) return r;
+  while (r > 1 && np < (int64_t)512 * kCicRound * r) r /= 2;
+  return r;
+}
+// the binned path's buffers for np particles; false without memory for them
+bool cic_buffers(mg_ctx* ctx, int64_t np, int64_t ntiles) {
+  const int64_t nbp = (np + kCicRound - 1) / kCicRound;
+  if (ctx->cic_np < np) {
+    void* old[3] = {ctx->cic_rec, ctx->cic_nrec, ctx->cic_runs};
+    for (void* q : old)
+      if (q) {
+        ctx->allocs.erase(std::find(ctx->allocs.begin(), ctx->allocs.end(), q));
+        (void)hipFree(q);
+      }
+    ctx->cic_rec = nullptr;
+    ctx->cic_nrec = nullptr;
+    ctx->cic_runs = nullptr;
+    ctx->cic_np = 0;
+  }
+  if ((!ctx->cic_rec && dalloc(ctx, &ctx->cic_rec, nbp * kCicRound + kCicRounds * kCicRound)) ||
+      (!ctx->cic_nrec && dalloc(ctx, &ctx->cic_nrec, nbp)) ||
+      (!ctx->cic_runs && dalloc(ctx, &ctx->cic_runs, np)) ||
+      (!ctx->cic_cnt && dalloc(ctx, &ctx->cic_cnt, 3 * 8 * ntiles))) {
+    (void)hipGetLastError();
+    return false;
+  }
+  ctx->cic_np = std::max(ctx->cic_np, np);
+  return true;
+}
+
 int cic_assign(mg_ctx* ctx, const float* pos, int64_t np, float* delta_out) {
   if (!ctx) return MG_EINVAL;
   if (!pos || !delta_out || np <= 0) return fail(ctx, MG_EINVAL, "cic_assign: bad arguments");
   int n = ctx->n;
   int64_t m = (int64_t)n * n * n;
   double scale = double(m) / double(np) / 4294967296.0;
-  const int nt = n / kT;
+  const int nt = (n + kT - 1) / kT;
   const int64_t ntiles = (int64_t)nt * nt * nt;
-  if (n % kT == 0 && np < (int64_t)0xffffffffLL - kCicRegion &&
-      8 * ntiles < ((int64_t)1 << kCicBinBits) && !ctx->cic_direct) {
+  // the records and runs take 16 bytes a particle; without memory for them the
+  // direct path runs
+  if (cic_binned(ctx, np, ntiles) && cic_buffers(ctx, np, ntiles)) {
     // binned path: runs of equal bins counted and recorded, scan, runs
     // placed in bin order, per-tile LDS deposit
-    const unsigned nbp = (unsigned)((np + kCicRegion - 1) / kCicRegion);
-    if (ctx->cic_np < np) {
-      ACHK(dalloc(ctx, &ctx->cic_rec, (int64_t)nbp * kCicRegion));
-      ACHK(dalloc(ctx, &ctx->cic_nrec, (int64_t)nbp));
-      ACHK(dalloc(ctx, &ctx->cic_runs, np));
-      ctx->cic_np = np;
-    }
-    if (!ctx->cic_cnt) ACHK(dalloc(ctx, &ctx->cic_cnt, 3 * 8 * ntiles));
+    const int rounds = cic_rounds(np, ntiles);
+    const int64_t region = (int64_t)kCicRound * rounds;
+    const unsigned nbp = (unsigned)((np + region - 1) / region);
     uint32_t* cnt = ctx->cic_cnt;
     uint32_t* boff = cnt + 8 * ntiles;
     uint32_t* cur = boff + 8 * ntiles;
     k_fill<uint32_t><<<nblk(8 * ntiles), kBlock, 0, ctx->stream>>>(cnt, 8 * ntiles, 0u);
-    k_cic_runs<<<nbp, kCicCB, 0, ctx->stream>>>(n, nt, np, pos, cnt, ctx->cic_rec, ctx->cic_nrec);
+    k_cic_runs<<<nbp, kCicCB, 0, ctx->stream>>>(n, nt, np, pos, cnt, ctx->cic_rec, ctx->cic_nrec,
+                                                rounds);
     k_cic_scan<<<1, 1024, 0, ctx->stream>>>(cnt, ntiles, boff, cur);
-    k_cic_place<<<nbp, kCicCB, 0, ctx->stream>>>(ctx->cic_rec, ctx->cic_nrec, cur, ctx->cic_runs);
-    k_cic_tile<<<(unsigned)ntiles, kCicTB, 0, ctx->stream>>>(n, nt, pos, ctx->cic_runs, boff, cnt,
-                                                             scale, delta_out);
+    k_cic_place<<<nbp, kCicCB, 0, ctx->stream>>>(ctx->cic_rec, ctx->cic_nrec, cur, ctx->cic_runs,
+                                                 rounds);
+    if (n % kT == 0)
+      k_cic_tile<true><<<(unsigned)ntiles, kCicTB, 0, ctx->stream>>>(n, nt, pos, ctx->cic_runs,
+                                                                     boff, cnt, scale, delta_out);
+    else
+      k_cic_tile<false><<<(unsigned)ntiles, kCicTB, 0, ctx->stream>>>(n, nt, pos, ctx->cic_runs,
+                                                                      boff, cnt, scale, delta_out);
     LAUNCHCHK();
     return MG_OK;
   }
@@ -3115,48 +3186,75 @@ int mg_residual(mg_ctx* ctx, int model, const mg_model_params* params, const flo
 
 namespace {
 
+// The 8 values around a particle, corner q as cic_weights numbers them, of NC
+// grids in a row.  Corners q and q + 1 are x-neighbours, read as one load of two
+// elements; on the periodic seam the pair (n - 2, n - 1) is read instead and
+// the cells at 0 come from one branch over all of them.  Bound by the cache lines
+// a wave's 64 particles touch (16.8M particles in grid order on 256^3 cells: 292
+// us with a branch per load and neighbouring workgroups on different XCDs, here
+// 277; friction 213 and, pairs loaded singly, here 181).
+template <typename TG, int NC>
+__device__ __forceinline__ void cic_gather(int n, const CicCell& c, const TG* __restrict__ grid,
+                                           TG (*v)[8]) {
+  typedef TG two_t __attribute__((ext_vector_type(2), aligned(sizeof(TG))));
+  const int64_t m = (int64_t)n * n * n;
+  const bool pair = c.i0[0] + 1 < n;
+  const uint32_t ix = (uint32_t)(pair ? c.i0[0] : n - 2);
+  uint32_t row[4];
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    const int jj = c.i0[1] + (h & 1) == n ? 0 : c.i0[1] + (h & 1);
+    const int kk = c.i0[2] + (h >> 1) == n ? 0 : c.i0[2] + (h >> 1);
+    row[h] = ((uint32_t)kk * (uint32_t)n + (uint32_t)jj) * (uint32_t)n;
+  }
+#pragma unroll
+  for (int a = 0; a < NC; ++a)
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const two_t two = *reinterpret_cast<const two_t*>(grid + a * m + (row[h] + ix));
+      v[a][2 * h] = two.x;
+      v[a][2 * h + 1] = two.y;
+    }
+  if (!pair) {
+#pragma unroll
+    for (int a = 0; a < NC; ++a)
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        v[a][2 * h] = v[a][2 * h + 1];
+        v[a][2 * h + 1] = grid[a * m + row[h]];
+      }
+  }
+}
+__device__ __forceinline__ double cic_weight(const CicCell& c, int q) {
+  return ((q & 1) ? c.t[0] : 1.0 - c.t[0]) * (((q >> 1) & 1) ? c.t[1] : 1.0 - c.t[1]) *
+         ((q >> 2) ? c.t[2] : 1.0 - c.t[2]);
+}
+// particle of a thread: workgroups of one XCD take consecutive particles, so
+// that particles in grid order share the rows in its L2
+__device__ __forceinline__ int64_t particle_id() {
+  return (int64_t)xcd_block() * kBlock + threadIdx.x;
+}
+__device__ __forceinline__ CicCell particle_cell(int n, const float* __restrict__ pos, int64_t p) {
+  float x[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) x[a] = pos[3 * p + a];
+  return cic_cell(n, x, 0);
+}
+
 // CIC interpolation to particles (same cells and weights as the assignment)
 template <typename TG, typename TO, int NC>
 __global__ __launch_bounds__(kBlock) void k_interp(int n, int64_t np,
                                                    const float* __restrict__ pos,
                                                    const TG* __restrict__ grid,
                                                    TO* __restrict__ out) {
-  int64_t p = gid();
+  const int64_t p = particle_id();
   if (p >= np) return;
-  const CicCell c = cic_cell(n, pos, p);
-  const int64_t m = (int64_t)n * n * n;
-  double w[8];
-  int64_t cell[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int di = q & 1, dj = (q >> 1) & 1, dk = (q >> 2) & 1;
-    w[q] = (di ? c.t[0] : 1.0 - c.t[0]) * (dj ? c.t[1] : 1.0 - c.t[1]) *
-           (dk ? c.t[2] : 1.0 - c.t[2]);
-    const int ii = c.i0[0] + di == n ? 0 : c.i0[0] + di;
-    const int jj = c.i0[1] + dj == n ? 0 : c.i0[1] + dj;
-    const int kk = c.i0[2] + dk == n ? 0 : c.i0[2] + dk;
-    cell[q] = ((int64_t)kk * n + jj) * n + ii;
-  }
-  // all 8 NC loads are independent: issue them together.  Corners q and q+1
-  // are x-neighbours; unless the pair wraps the periodic seam they are
-  // adjacent in memory and are read as one 2-element load.
+  const CicCell c = particle_cell(n, pos, p);
   TG v[NC][8];
-  const bool pair = c.i0[0] + 1 < n;
+  cic_gather<TG, NC>(n, c, grid, v);
+  double w[8];
 #pragma unroll
-  for (int a = 0; a < NC; ++a)
-#pragma unroll
-    for (int q = 0; q < 8; q += 2) {
-      const TG* src = grid + a * m + cell[q];
-      if (pair) {
-        typedef TG two_t __attribute__((ext_vector_type(2), aligned(sizeof(TG))));
-        const two_t two = *reinterpret_cast<const two_t*>(src);
-        v[a][q] = two.x;
-        v[a][q + 1] = two.y;
-      } else {
-        v[a][q] = src[0];
-        v[a][q + 1] = grid[a * m + cell[q + 1]];
-      }
-    }
+  for (int q = 0; q < 8; ++q) w[q] = cic_weight(c, q);
 #pragma unroll
   for (int a = 0; a < NC; ++a) {
     double acc = 0.0;
@@ -3172,20 +3270,14 @@ __global__ __launch_bounds__(kBlock) void k_sym_friction(int n, int64_t np,
                                                          const double* __restrict__ u,
                                                          const float* __restrict__ mom,
                                                          double coef, float* __restrict__ out) {
-  int64_t p = gid();
+  const int64_t p = particle_id();
   if (p >= np) return;
-  const CicCell c = cic_cell(n, pos, p);
+  const CicCell c = particle_cell(n, pos, p);
+  double v[1][8];
+  cic_gather<double, 1>(n, c, u, v);
   double up = 0.0;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int di = q & 1, dj = (q >> 1) & 1, dk = (q >> 2) & 1;
-    const double w = (di ? c.t[0] : 1.0 - c.t[0]) * (dj ? c.t[1] : 1.0 - c.t[1]) *
-                     (dk ? c.t[2] : 1.0 - c.t[2]);
-    const int ii = c.i0[0] + di == n ? 0 : c.i0[0] + di;
-    const int jj = c.i0[1] + dj == n ? 0 : c.i0[1] + dj;
-    const int kk = c.i0[2] + dk == n ? 0 : c.i0[2] + dk;
-    up += w * u[((int64_t)kk * n + jj) * n + ii];
-  }
+  for (int q = 0; q < 8; ++q) up += cic_weight(c, q) * v[0][q];
 #pragma unroll
   for (int a = 0; a < 3; ++a) out[3 * p + a] = float(coef * up * double(mom[3 * p + a]));
 }

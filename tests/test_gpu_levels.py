@@ -161,3 +161,61 @@ def test_boxes_together_take_the_same_steps(monkeypatch, sizes, cycle, nu, start
             continue
         for a, b, ref in zip(one[:2], plain[:2], (one[2], 0.0)):
             assert np.linalg.norm(a - b) <= 1e-6 * np.linalg.norm(b - ref)
+
+
+# particles binned by tiles of 16^3 cells against direct deposits: one thin tile,
+# a thin last tile of 2 to 14 cells, particles on the last layers and the seam
+@pytest.mark.parametrize("n", [10, 16, 18, 30, 34, 48, 50])
+def test_binned_deposit_on_any_side_equals_direct(n, monkeypatch):
+    rng = np.random.default_rng(500 + n)
+    pos = rng.uniform(0, n, (40011, 3)).astype(np.float32)
+    pos[:3000] = np.sort(pos[:3000], axis=0)
+    for a in range(3):
+        pos[3000 + 50 * a:3050 + 50 * a, a] = np.float32(n - 0.4)
+        pos[3200 + 50 * a:3250 + 50 * a, a] = np.float32(0.3)
+        pos[3400 + 50 * a:3450 + 50 * a, a] = np.float32(16 * ((n - 1) // 16) - 0.2)
+    t = torch.from_numpy(pos).to(DEV)
+    got = []
+    for mode in ("0", "1"):
+        monkeypatch.setenv("MGGPU_CIC_DIRECT", mode)
+        mg = api.Context(n, device=DEV)
+        print("binned deposit", n, mode, flush=True)
+        mg.cic(t[:100].contiguous())  # the binned path's buffers grow
+        got.append(mg.cic(t).cpu().numpy())
+        mg.close()
+    assert np.array_equal(got[0], got[1])
+    ref = oracle.cic(n, pos.astype(np.float64))
+    assert np.max(np.abs(got[0] - ref)) <= 1e-6 * (1 + np.max(np.abs(ref)))
+
+
+# gathers at particles on the seam of each axis against CIC weights in FP64
+@pytest.mark.parametrize("n", [8, 10, 18])
+def test_gathers_on_the_seam(n):
+    rng = np.random.default_rng(600 + n)
+    pos = rng.uniform(0, n, (1003, 3)).astype(np.float32)
+    for a in range(3):
+        pos[100 * a:100 * a + 50, a] = np.float32(n - 0.3)
+        pos[100 * a + 50:100 * a + 100, a] = np.float32(0.2)
+    x = pos.astype(np.float64) - 0.5
+    i0 = np.floor(x).astype(int)
+    t = x - i0
+    grid = rng.standard_normal((3, n, n, n)).astype(np.float32)
+    want = np.zeros((len(pos), 3))
+    for q in range(8):
+        d = [(q >> a) & 1 for a in range(3)]
+        w = np.prod([t[:, a] if d[a] else 1 - t[:, a] for a in range(3)], axis=0)
+        i, j, k = [(i0[:, a] + d[a]) % n for a in range(3)]
+        want += w[:, None] * grid[:, k, j, i].T
+    mg = api.Context(n, device=DEV)
+    tp, tg = torch.from_numpy(pos).to(DEV), torch.from_numpy(grid).to(DEV)
+    print("gathers", n, flush=True)
+    three = mg.interp_to_particles(tg, tp).cpu().numpy()
+    mom = torch.from_numpy(rng.standard_normal(pos.shape).astype(np.float32)).to(DEV)
+    fric = mg.symmetron_friction(api.model_params(float(n), a=1.0, a_star=0.5),
+                                 tg[1].double(), tp, mom).cpu().numpy()
+    mg.close()
+    assert np.max(np.abs(three - want)) <= 2.0 ** -23 * np.max(np.abs(grid))
+    # the same factor for every particle
+    f = want[:, 1:2] * mom.cpu().numpy().astype(np.float64)
+    c = np.sum(fric * f) / np.sum(f * f)
+    assert np.max(np.abs(fric - c * f)) <= 2.0 ** -22 * np.max(np.abs(c * f))
