@@ -354,13 +354,18 @@ void launch_unpack(mg_ctx* ctx, const Lev& L, const TI* pk, TO* nat, double scal
 
 // v += P(c - c2) (c2 may be null): the z-marching kernel when the coarse
 // side is a multiple of 4 (the caller guarantees nc % Vec<T>::V == 0)
-constexpr int kProlongKT = 4;  // coarse planes per marching thread
+// coarse planes per marching thread; fewer where the grid would not fill the
+// chip and each plane's dependent loads bound it (FP64, 40^3 -> 80^3: 14.6 us
+// with 4; FP32, 48^3 -> 96^3 14.7 with 4, 5.4 with 1)
+constexpr int kProlongKT = 4;
 constexpr int kRestrictKT = 4;
 template <typename T, int COL0>
 void launch_prolong(mg_ctx* ctx, const Lev& Lf, const Lev& Lc, T* v, const T* c, const T* c2) {
   if (Lc.n % 4 == 0 && Lc.n >= 8) {
-    k_prolong_kv<T, COL0><<<prolong_march_blocks(Lc.n, kProlongKT), kBlock, 0, ctx->stream>>>(
-        Lf, Lc, v, c, c2, kProlongKT);
+    int kt = kProlongKT;
+    while (kt > 1 && prolong_march_blocks(Lc.n, kt) < kMarchMinBlocks) kt /= 2;
+    k_prolong_kv<T, COL0><<<prolong_march_blocks(Lc.n, kt), kBlock, 0, ctx->stream>>>(
+        Lf, Lc, v, c, c2, kt);
   } else {
     k_prolong_v<T, COL0><<<nblk(cells(Lc) / Vec<T>::V), kBlock, 0, ctx->stream>>>(Lf, Lc, v, c,
                                                                                   c2);
@@ -1109,6 +1114,8 @@ bool use_mid(const mg_ctx* ctx, const mg_solver_opts* o, int l) {
          o->nu_pre == 1 && o->nu_post == 1 && !(l == 0 && ctx->prof);
 }
 
+constexpr int kCqPerCellN = 64;  // see the restriction in cycle32
+
 // rx: restrict the linearisation point X on the way down (first cycle of
 // an outer step)
 template <int M>
@@ -1195,7 +1202,10 @@ int cycle32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
                 W.rho[l + 1], W.X[l + 1], C, kRestrictKT, S, Xf, rxi);
       });
     });
-  else if (vec)
+  // CQ's residuals (exp and log of every cell) bound 4 coarse cells per thread
+  // on small levels: 18.7 us against 8.9 per cell at 96^3, 16.7 against 7.8 at
+  // 24^3; at 192^3 the two are equal
+  else if (vec && !(M == CQ && Lc.n <= kCqPerCellN))
     with_level_store(ctx, l, [&](auto* X, auto* R) {
       using TX = std::remove_pointer_t<decltype(X)>;
       using TR = std::remove_pointer_t<decltype(R)>;
