@@ -1177,7 +1177,8 @@ __device__ __forceinline__ void march_nbsum(const Lev& L, const double* __restri
     sum[q] = (xv[q] + xv[q + 1]) + (ym[q] + yp[q]) + (wo[0][q] + wo[2][q]);
 }
 
-// (every thread of the workgroup calls it; sh: 32 doubles of LDS)
+// (every thread of the workgroup calls it; sh: 32 doubles of LDS; rho null: no
+// cycle follows, rho and X are not written)
 template <int M, typename TX, typename TR>
 __device__ __forceinline__ void op_outer_fused_kv(
     const Lev& L, const double* __restrict__ w, const float* __restrict__ e,
@@ -1225,8 +1226,10 @@ __device__ __forceinline__ void op_outer_fused_kv(
           xo[q] = float(vc);
           zo[q] = 0.0f;
         }
-        st4s<TR>(rho + q0, ro, S.r_enc);
-        st4s<TX>(X + q0, xo, S.x_enc);
+        if (rho) {
+          st4s<TR>(rho + q0, ro, S.r_enc);
+          st4s<TX>(X + q0, xo, S.x_enc);
+        }
         if (e_zero) stn_nt<float, V>(e_zero + q0, zo);
       }
 #pragma unroll
@@ -2364,6 +2367,24 @@ __global__ __launch_bounds__(kBlock) void k_bg_norm(int64_t m, const float* delt
   int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   double d = g < m ? coef * double(delta[g]) : 0.0;
   double t = block_sum(d * d, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
+}
+// the same on 16-byte aligned arrays, kBgPer vectors per thread (384^3: 144 us
+// with one cell per thread, mostly its block sums)
+constexpr int kBgPer = 4;
+__global__ __launch_bounds__(kBlock) void k_bg_norm4(int64_t m4, const float4* delta, double coef,
+                                                    double* part) {
+  __shared__ double sh[32];
+  double s = 0.0;
+#pragma unroll
+  for (int q = 0; q < kBgPer; ++q) {
+    const int64_t g = ((int64_t)blockIdx.x * kBgPer + q) * kBlock + threadIdx.x;
+    const float4 v = g < m4 ? delta[g] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const double a = coef * double(v.x), b = coef * double(v.y), c = coef * double(v.z),
+                 d = coef * double(v.w);
+    s += a * a + b * b + c * c + d * d;
+  }
+  const double t = block_sum(s, sh);
   if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 

@@ -719,10 +719,17 @@ inline double bg_norm_of(const Consts& C, double r) {
 
 int bg_rms(mg_ctx* ctx, const Consts& C, const float* delta, double* out) {
   int64_t m = cells(ctx->L[0]);
-  k_bg_norm<<<nblk(m), kBlock, 0, ctx->stream>>>(m, delta, C.bg_coef, ctx->part);
+  int64_t nparts = nblk(m);
+  if (al16(delta)) {
+    nparts = (m / 4 + kBgPer * kBlock - 1) / (kBgPer * kBlock);
+    k_bg_norm4<<<(unsigned)nparts, kBlock, 0, ctx->stream>>>(
+        m / 4, reinterpret_cast<const float4*>(delta), C.bg_coef, ctx->part);
+  } else {
+    k_bg_norm<<<(unsigned)nparts, kBlock, 0, ctx->stream>>>(m, delta, C.bg_coef, ctx->part);
+  }
   LAUNCHCHK();
   double s;
-  ACHK(sum_to_host(ctx, nblk(m), &s));
+  ACHK(sum_to_host(ctx, nparts, &s));
   *out = bg_norm_of(C, sqrt(s / double(m)));
   return MG_OK;
 }
@@ -1342,7 +1349,9 @@ int solve32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const float* 
       // (at a uniform start bg_coef delta, whose delta = 1 then maps to 1;
       // after cycles 1/100 of the last check's); a pass whose largest |rho|
       // would overflow is redone with the scale its maximum allows
-      const bool r16 = f16 && (uni || outer > 0);
+      // (a fixed number of cycles ends with this residual)
+      const bool last = fixed && outer > 0;
+      const bool r16 = f16 && (uni || outer > 0) && !last;
       double rms_pred = outer == 0 ? 16.0 * C.bg_coef : rel * eps_bg * 1e-2;
       int rexp = r16 ? (int)lround(log2(16.0 / (rms_pred > 0.0 ? rms_pred : 1.0))) : 0;
       for (int pass = 0;; ++pass) {
@@ -1359,7 +1368,7 @@ int solve32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, const float* 
           using TR = std::remove_pointer_t<decltype(R)>;
           with_n<M>(C, [&](auto N) {
             k_outer_fused_kv<M, N, TX, TR><<<(unsigned)nparts, kBlock, 0, ctx->stream>>>(
-                L0, wsrc, pending, wn, W.dens[0], C, R, X, ez, ctx->part,
+                L0, wsrc, pending, wn, W.dens[0], C, last ? nullptr : R, X, ez, ctx->part,
                 bgsum ? ctx->part3 : nullptr, mkt, ctx->s0.S, r16 ? ctx->part4 : nullptr);
           });
         });
