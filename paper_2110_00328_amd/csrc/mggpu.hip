@@ -3077,30 +3077,33 @@ int cic_rounds(int64_t np, int64_t ntiles) {
   while (r > 1 && np < (int64_t)512 * kCicRound * r) r /= 2;
   return r;
 }
-// the binned path's buffers for np particles; false without memory for them
+// The binned path's buffers for np particles, one allocation; false without
+// memory for them.  Larger ones are added for a larger deposit: a graph captured
+// from an earlier one still uses the earlier buffers, so those live until the
+// context's end.  From the second time on half as much again is taken, so that
+// deposits that keep growing add few.
 bool cic_buffers(mg_ctx* ctx, int64_t np, int64_t ntiles) {
-  const int64_t nbp = (np + kCicRound - 1) / kCicRound;
-  if (ctx->cic_np < np) {
-    void* old[3] = {ctx->cic_rec, ctx->cic_nrec, ctx->cic_runs};
-    for (void* q : old)
-      if (q) {
-        ctx->allocs.erase(std::find(ctx->allocs.begin(), ctx->allocs.end(), q));
-        (void)hipFree(q);
-      }
-    ctx->cic_rec = nullptr;
-    ctx->cic_nrec = nullptr;
-    ctx->cic_runs = nullptr;
-    ctx->cic_np = 0;
-  }
-  if ((!ctx->cic_rec && dalloc(ctx, &ctx->cic_rec, nbp * kCicRound + kCicRounds * kCicRound)) ||
-      (!ctx->cic_nrec && dalloc(ctx, &ctx->cic_nrec, nbp)) ||
-      (!ctx->cic_runs && dalloc(ctx, &ctx->cic_runs, np)) ||
-      (!ctx->cic_cnt && dalloc(ctx, &ctx->cic_cnt, 3 * 8 * ntiles))) {
+  if (ctx->cic_np >= np) return true;
+  auto up = [](int64_t b) { return (b + 255) & ~(int64_t)255; };
+  const std::string err = ctx->err;
+  for (int64_t cap = std::max(np, ctx->cic_np + ctx->cic_np / 2);; cap = np) {
+    const int64_t nbp = (cap + kCicRound - 1) / kCicRound;
+    const int64_t rec = up((nbp * kCicRound + kCicRounds * kCicRound) * (int64_t)sizeof(uint2));
+    const int64_t runs = up(cap * (int64_t)sizeof(unsigned long long));
+    const int64_t nrec = up(nbp * (int64_t)sizeof(uint32_t));
+    char* base = nullptr;
+    if (dalloc(ctx, &base, rec + runs + nrec + 3 * 8 * ntiles * (int64_t)sizeof(uint32_t)) == MG_OK) {
+      ctx->cic_rec = (uint2*)base;
+      ctx->cic_runs = (unsigned long long*)(base + rec);
+      ctx->cic_nrec = (uint32_t*)(base + rec + runs);
+      ctx->cic_cnt = (uint32_t*)(base + rec + runs + nrec);
+      ctx->cic_np = cap;
+      return true;
+    }
     (void)hipGetLastError();
-    return false;
+    ctx->err = err;
+    if (cap == np) return false;
   }
-  ctx->cic_np = std::max(ctx->cic_np, np);
-  return true;
 }
 
 int cic_assign(mg_ctx* ctx, const float* pos, int64_t np, float* delta_out) {
