@@ -25,6 +25,7 @@
 #include <dlfcn.h>
 #include <rocfft/rocfft.h>  // declarations only: the library is opened at first use
 
+#include "cic_path.h"
 #include "mg_batched.h"
 #include "mg_grouped.h"
 #include "mg_kernels.h"
@@ -3043,6 +3044,16 @@ const char* mg_last_error(const mg_ctx* ctx) { return ctx ? ctx->err.c_str() : "
 
 int mg_ctx_levels(const mg_ctx* ctx) { return ctx ? ctx->nlev : 0; }
 
+}  // extern "C"
+
+namespace {
+
+// the binned path's particle and bin numbers fit its records
+bool cic_binnable(int64_t np, int64_t ntiles) {
+  return np < (int64_t)0xffffffffLL - kCicRound * kCicRounds &&
+         8 * ntiles < ((int64_t)1 << kCicBinBits);
+}
+
 // Whether np particles are binned by tiles rather than deposited with global
 // atomics.  Those take 0.24 (grid order) to 0.35 ns (no order) a particle and
 // little else (8^3 to 32^3 cells: 13-20 us in all); the binned path takes five
@@ -3055,9 +3066,7 @@ int mg_ctx_levels(const mg_ctx* ctx) { return ctx ? ctx->nlev : 0; }
 // / 354 at 100^3.  48^3 cells (27 tiles, none thin) repay it in grid order from 8
 // particles a cell on (182 / 217).
 bool cic_binned(const mg_ctx* ctx, int64_t np, int64_t ntiles) {
-  if (ctx->cic_direct == 1 || np >= (int64_t)0xffffffffLL - kCicRound * kCicRounds ||
-      8 * ntiles >= ((int64_t)1 << kCicBinBits))
-    return false;
+  if (ctx->cic_direct == 1 || !cic_binnable(np, ntiles)) return false;
   if (ctx->cic_direct == 0) return true;
   const int64_t full = cells(ctx->L[0]) / kT3;  // in full tiles
   const bool even = ctx->n % kT == 0;           // no thin ones
@@ -3106,6 +3115,20 @@ bool cic_buffers(mg_ctx* ctx, int64_t np, int64_t ntiles) {
   }
 }
 
+// the direct path's accumulator; false without memory for it
+bool cic_accumulator(mg_ctx* ctx) {
+  if (ctx->cic) return true;
+  const std::string err = ctx->err;
+  if (dalloc(ctx, &ctx->cic, cells(ctx->L[0])) == MG_OK) return true;
+  (void)hipGetLastError();
+  ctx->err = err;
+  return false;
+}
+
+}  // namespace
+
+extern "C" {
+
 int cic_assign(mg_ctx* ctx, const float* pos, int64_t np, float* delta_out) {
   if (!ctx) return MG_EINVAL;
   if (!pos || !delta_out || np <= 0) return fail(ctx, MG_EINVAL, "cic_assign: bad arguments");
@@ -3114,9 +3137,24 @@ int cic_assign(mg_ctx* ctx, const float* pos, int64_t np, float* delta_out) {
   double scale = double(m) / double(np) / 4294967296.0;
   const int nt = (n + kT - 1) / kT;
   const int64_t ntiles = (int64_t)nt * nt * nt;
-  // the records and runs take 16 bytes a particle; without memory for them the
-  // direct path runs
-  if (cic_binned(ctx, np, ntiles) && cic_buffers(ctx, np, ntiles)) {
+  // the faster path, unless its buffers are missing (cic_takes_binned) or memory
+  // for them is; MGGPU_CIC_DIRECT leaves only the second
+  const int mode = ctx->cic_direct;
+  bool binned = cic_binned(ctx, np, ntiles);
+  if (mode < 0 && cic_binnable(np, ntiles)) {
+    const bool have_b = ctx->cic_np >= np, have_d = ctx->cic != nullptr;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (binned && !have_b && have_d && hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess)
+      (void)hipGetLastError();
+    binned = cic_takes_binned(binned, have_b, have_d, cap != hipStreamCaptureStatusNone);
+    if (binned && cic_makes_both(n)) (void)cic_accumulator(ctx);
+  }
+  if (binned) binned = cic_buffers(ctx, np, ntiles);
+  if (!binned && !cic_accumulator(ctx)) {
+    if (mode != 1 && cic_binnable(np, ntiles)) binned = cic_buffers(ctx, np, ntiles);
+    if (!binned) return fail(ctx, MG_EHIP, "cic_assign: no device memory for the deposit");
+  }
+  if (binned) {
     // binned path: runs of equal bins counted and recorded, scan, runs
     // placed in bin order, per-tile LDS deposit
     const int rounds = cic_rounds(np, ntiles);
@@ -3140,7 +3178,6 @@ int cic_assign(mg_ctx* ctx, const float* pos, int64_t np, float* delta_out) {
     LAUNCHCHK();
     return MG_OK;
   }
-  if (!ctx->cic) ACHK(dalloc(ctx, &ctx->cic, m));
   unsigned long long* acc = (unsigned long long*)ctx->cic;
   k_fill<unsigned long long><<<nblk(m), kBlock, 0, ctx->stream>>>(acc, m, 0ull);
   k_cic<<<nblk(np), kBlock, 0, ctx->stream>>>(n, np, pos, acc);

@@ -51,3 +51,28 @@ def test_captured_deposit_outlives_larger_ones(n, monkeypatch):
             assert torch.equal(out, want) and torch.equal(mg.cic(p), r)
         assert all(bool((t == 3).all()) for t in taken)
         mg.close()
+
+
+# a deposit under capture, where nothing can be allocated, after one of other
+# size: fewer particles on any side, more on sides of no multiple of 16
+@pytest.mark.parametrize("n,before,count", [(64, 300000, 1000), (66, 300000, 1000),
+                                            (66, 1000, 300000), (66, 300000, 700000)])
+def test_deposits_of_other_sizes_can_be_captured(n, before, count):
+    stream = torch.cuda.Stream()
+    first, pos = uniform(n, before, 11), uniform(n, count, 12)
+    print("captured deposit of another size", n, before, count, flush=True)
+    plain = api.Context(n, device=DEV)
+    want = plain.cic(pos)
+    plain.close()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        mg = api.Context(n, device=DEV, stream=stream)
+        again = mg.cic(first).clone()
+        out = torch.empty((n, n, n), device=DEV)
+        graph = captured(mg, stream, pos, out)
+        for _ in range(3):
+            out.fill_(-7.0)
+            graph.replay()
+            assert torch.equal(out, want)
+            assert torch.equal(mg.cic(first), again)
+        mg.close()
