@@ -3054,25 +3054,9 @@ bool cic_binnable(int64_t np, int64_t ntiles) {
          8 * ntiles < ((int64_t)1 << kCicBinBits);
 }
 
-// Whether np particles are binned by tiles rather than deposited with global
-// atomics.  Those take 0.24 (grid order) to 0.35 ns (no order) a particle and
-// little else (8^3 to 32^3 cells: 13-20 us in all); the binned path takes five
-// dependent launches (25-35 us) and then 5 to 13.5 ns a particle in each full
-// tile, tiles in parallel, so it needs many tiles (counted in full ones) and
-// many particles.  Binned / direct, us: 64^3 cells 51 / 68 at 64^3 particles, 24
-// / 17 at 32^3; 100^3 cells 30 / 47 at 50^3, 70 / 262 at 100^3; 200^3 cells, no
-// order, 100^3 particles 163 / 373; 32^3 cells (8 tiles) 157 / 67 at 64^3; in no
-// order 62^3 cells 85 / 90 at 62^3, 58^3 (48 tiles) 82 / 75 at 58^3, 50^3 (31) 431
-// / 354 at 100^3.  48^3 cells (27 tiles, none thin) repay it in grid order from 8
-// particles a cell on (182 / 217).
 bool cic_binned(const mg_ctx* ctx, int64_t np, int64_t ntiles) {
   if (ctx->cic_direct == 1 || !cic_binnable(np, ntiles)) return false;
-  if (ctx->cic_direct == 0) return true;
-  const int64_t full = cells(ctx->L[0]) / kT3;  // in full tiles
-  const bool even = ctx->n % kT == 0;           // no thin ones
-  if (full >= (even ? 64 : 125)) return np >= (1 << 17);
-  if (full >= 56) return np >= (3 << 16);
-  return even && full >= 27 && np >= (1 << 19);
+  return ctx->cic_direct == 0 || cic_prefers_binned(ctx->n, np);
 }
 
 // Rounds per region of the binned path: all of them where a tile holds many
