@@ -21,7 +21,7 @@ namespace mgg {
 inline bool cic_prefers_binned(int n, int64_t np) {
   const double m = double(n) * n * n, p = double(np), per_tile = p / (m / 4096.0);
   if (n % 16 == 0) return 0.22 * p - 5.0 * per_tile + 1.0e-3 * m > 1.0e4;
-  return 0.24 * p - 10.0 * per_tile + 0.5e-3 * m > 1.8e4;
+  return 0.24 * p - 10.0 * per_tile + 0.5e-3 * m > 1.75e4;
 }
 
 // Whether a deposit takes the binned path, given the faster path (want_binned)
