@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mg_arith.h"
+
 namespace mgg {
 
 enum { FR = 0, SYM = 1, CQ = 2 };
@@ -168,11 +170,10 @@ __device__ __forceinline__ float cubic_root_approx(float p, float q) {
 }
 
 // FP64 root of t^3 + p t + q = 0 with q < 0 (unique positive root): FP32
-// start, two FP64 Newton steps (quadratic from ~1e-5: ~1e-20); falls back to
-// the FP64 closed form when the start is not usable.  The steps multiply by the
-// hardware reciprocal (relative error d < 1e-7): the second one starts within
-// 1e-10 + 1e-5 d and adds 1e-10 d, far below FP64 rounding, at a sixth of the
-// dependent operations of a division.
+// start, two FP64 Newton steps (the start is off by up to 1e-6 of the root, or
+// 3e-4 around |x| = 1e-3, where the cubic is nearly linear: the second step's
+// error is below 1e-16 in both); falls back to the FP64 closed form when the
+// start is not usable.
 __device__ __forceinline__ double cubic_root_pos64(double p, double q) {
   float t0 = cubic_root_approx(float(p), float(q));
   if (!(t0 > 0.0f) || !isfinite(t0)) return cubic_root<double>(p, q);
@@ -181,7 +182,7 @@ __device__ __forceinline__ double cubic_root_pos64(double p, double q) {
   for (int it = 0; it < 2; ++it) {
     double f = (t * t + p) * t + q;
     double fp = 3.0 * t * t + p;
-    t -= f * __builtin_amdgcn_rcp(fp);
+    t -= quotient(f, fp, [](double x) { return __builtin_amdgcn_rcp(x); });
   }
   return t;
 }
@@ -238,7 +239,7 @@ __device__ __forceinline__ T direct_update(const Consts& C, T h2, T vc, T sum, T
   if constexpr (M == FR) {
     // u^{n+2} + p u + q = 0, w = u^{n+1} (eq:fR_eom_codeunit; S shifts p)
     T g = h2 / (T(6) * T(C.ct2));
-    T p = g * (T(C.om_a) * dc + T(C.K) - sc) - sum * T(1.0 / 6.0);
+    T p = g * (T(C.om_a) * dc + T(C.K) - sc) - sixth(sum);
     T q = -g * T(C.K) * T(C.wpow);
     if (C.fr_n == 1) {
       T u;
