@@ -219,3 +219,51 @@ def test_gathers_on_the_seam(n):
     f = want[:, 1:2] * mom.cpu().numpy().astype(np.float64)
     c = np.sum(fric * f) / np.sum(f * f)
     assert np.max(np.abs(fric - c * f)) <= 2.0 ** -22 * np.max(np.abs(c * f))
+
+
+# The level kernels that run one operation each, which levels of at most 80
+# cells a side reach only without the one-launch form: marching in z against one
+# plane per thread (restriction, smoother), and the prolongation formed inside
+# the half-sweep (f(R) and adjoint) against the two kernels.  Bit for bit the
+# same.  64^3: coarse sides 32 and 16, one tile of whole rows; 96^3: 48, 24,
+# ragged last tiles; 160^3: 80, 40, 20; 3 planes leave a ragged last chunk.
+MARCH = dict(MGGPU_MARCH_MIN_BLOCKS="0", MGGPU_SMOOTH_MARCH_KT="4")
+PLANE = dict(MGGPU_MARCH_MIN_BLOCKS="2147483647", MGGPU_SMOOTH_MARCH_KT="0")
+
+
+def same_with(monkeypatch, model, n, fp16, envs):
+    _, prm, delta = inputs(model, n, 93)
+    dt = torch.from_numpy(delta).to(DEV)
+    gv = torch.from_numpy(np.random.default_rng(94).standard_normal((n, n, n))).to(DEV)
+    monkeypatch.setenv("MGGPU_MID_MAX_N", "0")
+    monkeypatch.setenv("MGGPU_FP16_STORAGE", fp16)
+    got = []
+    for env in envs:
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        mg = api.Context(n, device=DEV)
+        print("separate level kernels", model, n, fp16, env, flush=True)
+        field, _ = mg.solve(model, prm, dt, tol=1e-8)
+        gd, _ = mg.solve_adjoint(model, prm, dt, field, gv, tol=1e-8)
+        got.append((field, gd))
+        mg.close()
+    assert torch.equal(got[0][0], got[1][0])
+    assert torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("model,n,fp16", [("fr", 64, "1"), ("sym", 64, "0"), ("fr", 96, "0"),
+                                          ("sym", 96, "1"), ("fr", 160, "1")])
+def test_marching_level_kernels_below_the_one_launch_limit(monkeypatch, model, n, fp16):
+    monkeypatch.setenv("MGGPU_PROLONG_SMOOTH_KT", "0")
+    same_with(monkeypatch, model, n, fp16, (PLANE, MARCH))
+
+
+@pytest.mark.parametrize("model,n,kt,fp16", [("fr", 64, "1", "1"), ("fr", 64, "2", "0"),
+                                             ("fr", 96, "4", "1"), ("fr", 96, "8", "0"),
+                                             ("fr", 160, "3", "0"), ("sym", 96, "4", "1")])
+def test_fused_prolongation_below_the_one_launch_limit(monkeypatch, model, n, kt, fp16):
+    for k, v in MARCH.items():
+        monkeypatch.setenv(k, v)
+    monkeypatch.setenv("MGGPU_PROLONG_SMOOTH_MIN_BLOCKS", "0")
+    same_with(monkeypatch, model, n, fp16,
+              [dict(MGGPU_PROLONG_SMOOTH_KT=k) for k in ("0", kt)])
