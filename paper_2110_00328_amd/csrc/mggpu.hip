@@ -4481,8 +4481,11 @@ std::string batch_key(mg_ctx* ctx, int nb, const mg_box_desc* boxes, const mg_so
     parts.push_back(std::to_string(boxes[b].n) + (boxes[b].model == MG_FR ? "f" :
                                                   boxes[b].model == MG_SYMMETRON ? "s" : "q"));
   std::sort(parts.begin(), parts.end());
-  // the multiset of (n, model): counts matter for the team split
-  std::string k = "batched2:";
+  // the multiset of (n, model): counts matter for the team split.  The number goes
+  // up when kernels of either design get faster: an entry of an earlier library
+  // chose by times that are no longer true (12 boxes of 32^3-64^3: the persistent
+  // launch at 4.2 ms, where the grouped ones now take 2.2).
+  std::string k = "batched3:";
   for (size_t q = 0; q < parts.size();) {
     size_t r = q;
     while (r < parts.size() && parts[r] == parts[q]) ++r;
@@ -4591,11 +4594,13 @@ int mg_batched_tune(mg_ctx* ctx, int n_box, const mg_box_desc* boxes, const mg_s
       }
     }
   }
-  // The persistent launch is cooperative, and any cooperative launch slows
-  // the grouped path for the rest of the process: the 64-box 64^3..128^3
-  // batch then takes 16.6 instead of 11.8 ms, about its time with the class
-  // streams serialised.  So it is only tried for batches too small to fill
-  // the chip with level launches (below 8M cells in all), where it can win.
+  // The persistent launch is tried for batches too small to fill the chip with
+  // level launches (below 8M cells in all), where it can win (40 boxes of
+  // 16^3-32^3: a tie at 2.0-2.3 ms; 12 of 32^3-64^3 4.2 against 2.2, 6 of 96^3 8.5
+  // against 1.6).  It is cooperative, and class streams that have done no work
+  // before a process's first cooperative launch overlap worse for good (64 boxes
+  // of 64^3-128^3 13.8 ms instead of 10.1, 6 of 96^3 2.6 instead of 1.6); after
+  // the grouped launches above it costs them nothing (10.1, 1.6).
   int64_t batch_cells = 0;
   for (int b = 0; b < n_box; ++b) batch_cells += (int64_t)boxes[b].n * boxes[b].n * boxes[b].n;
   if (batch_cells < ((int64_t)8 << 20))

@@ -5,6 +5,8 @@ Tolerances as for the other parity tests: both sides are converged far below
 the target, so FP64 solves agree to 1e-8 and FP32-refined ones to 1e-6
 (relative to the deviation from the background), adjoints to 1e-8 and 1e-5.
 """
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -267,3 +269,26 @@ def test_fused_prolongation_below_the_one_launch_limit(monkeypatch, model, n, kt
     monkeypatch.setenv("MGGPU_PROLONG_SMOOTH_MIN_BLOCKS", "0")
     same_with(monkeypatch, model, n, fp16,
               [dict(MGGPU_PROLONG_SMOOTH_KT=k) for k in ("0", kt)])
+
+
+# a tuning file of a library with other kernels is not taken: the batch is tuned
+# again and the entry stays beside the new one
+def test_earlier_tuning_is_not_taken(monkeypatch, tmp_path):
+    path = tmp_path / "tune.json"
+    monkeypatch.setenv("MGGPU_TUNE_CACHE", str(path))
+    _, prm, d = inputs("fr", 16, 97)
+    field = torch.empty((16, 16, 16), dtype=torch.float64, device=DEV)
+    box = dict(n=16, model="fr", params=prm, delta=torch.from_numpy(d).to(DEV), field=field)
+
+    def keys():
+        print("earlier tuning", flush=True)
+        mg = api.Context(16, device=DEV)
+        mg.solve_batched([box], tol=1e-6)
+        mg.close()
+        return [line.split('"')[1] for line in path.read_text().splitlines() if '"' in line]
+
+    (key,) = keys()
+    earlier = re.sub(r"batched\d+:", "batched2:", key)
+    assert earlier != key
+    path.write_text('{\n  "%s": [1024, 0, 0, 0.001]\n}\n' % earlier)
+    assert sorted(keys()) == sorted([earlier, key])
