@@ -169,6 +169,9 @@ struct mg_ctx {
   // batched solves
   void* bpool = nullptr;
   size_t bpool_bytes = 0;
+  // grouped solves: pools of this size or more have been refused
+  // (MGGPU_TEST_BATCH_POOL at context creation sets it from the host, for tests)
+  size_t bpool_refused = SIZE_MAX;
   BoxDev* bdev = nullptr;
   BoxOut* bout = nullptr;
   int bcap = 0;
@@ -2950,6 +2953,7 @@ int mg_ctx_create(mg_ctx** out, int n, void* hip_stream) {
   if (const char* mb = getenv("MGGPU_MARCH_MIN_BLOCKS")) ctx->march_min_blocks = (unsigned)atoi(mb);
   if (const char* cd = getenv("MGGPU_CIC_DIRECT")) ctx->cic_direct = atoi(cd) != 0 ? 1 : 0;
   if (const char* ts = getenv("MGGPU_TEST_CORRECTION_SCALE")) ctx->test_escale = (float)atof(ts);
+  if (const char* bp = getenv("MGGPU_TEST_BATCH_POOL")) ctx->bpool_refused = (size_t)atoll(bp);
   if (const char* fs = getenv("MGGPU_FP16_STORAGE")) ctx->fp16 = atoi(fs) != 0;
   if (const char* pk = getenv("MGGPU_PROLONG_SMOOTH_KT")) {
     const int kt = atoi(pk);
@@ -4223,18 +4227,26 @@ int grouped_solve(mg_ctx* ctx, int nb, const mg_box_desc* boxes, const mg_solver
   size_t extra = 0;
   for (size_t c = 0; c < cls.size(); ++c)
     extra += (size_t)cls[c].count * g_extra_bytes(ctx, cls[c], &levs[c * kMaxLevB]);
-  if (total + extra > ctx->bpool_bytes) {
+  auto pool = [&](size_t bytes) {
     if (ctx->bpool) (void)hipFree(ctx->bpool);
     ctx->bpool = nullptr;
     ctx->bpool_bytes = 0;
-    if (hipMalloc(&ctx->bpool, total + extra) != hipSuccess) {
+    const hipError_t e = hipMalloc(&ctx->bpool, bytes);
+    if (e == hipSuccess) ctx->bpool_bytes = bytes;
+    else ctx->bpool = nullptr;
+    return e;
+  };
+  bool full = total + extra <= ctx->bpool_bytes;
+  if (!full && total + extra < ctx->bpool_refused) {
+    full = pool(total + extra) == hipSuccess;
+    if (!full) {  // later calls keep what they get below instead of trying again
       (void)hipGetLastError();
-      ctx->bpool = nullptr;
-      for (GClass& K : cls) K.march = K.mid = 0;
-      extra = 0;
-      HIPCHK(hipMalloc(&ctx->bpool, total));
+      ctx->bpool_refused = total + extra;
     }
-    ctx->bpool_bytes = total + extra;
+  }
+  if (!full) {
+    for (GClass& K : cls) K.march = K.mid = 0;
+    if (total > ctx->bpool_bytes) HIPCHK(pool(total));
   }
   ACHK(g_grow(ctx, nb, pstride));
   const int ns = std::min((int)cls.size(), (int)mg_ctx::kGStreams);

@@ -292,3 +292,36 @@ def test_earlier_tuning_is_not_taken(monkeypatch, tmp_path):
     assert earlier != key
     path.write_text('{\n  "%s": [1024, 0, 0, 0.001]\n}\n' % earlier)
     assert sorted(keys()) == sorted([earlier, key])
+
+
+# boxes together without memory for the second masters and the one-launch levels'
+# scratch (refused from the host): the separate kernels, which boxes at odd
+# addresses take too, on every call
+def test_boxes_together_in_the_smaller_pool(monkeypatch):
+    got = []
+    for refused, off in (("1", 0), (None, 1)):
+        if refused:
+            monkeypatch.setenv("MGGPU_TEST_BATCH_POOL", refused)
+        else:
+            monkeypatch.delenv("MGGPU_TEST_BATCH_POOL")
+            monkeypatch.setenv("MGGPU_MID_MAX_N", "0")
+        mg = api.Context(8, device=DEV)
+        mg.batched_set_config(256, 1, 2)
+        for sizes in ((32, 24), (16, 16), (32, 24, 40)):  # the pool grows, is kept, grows
+            boxes = []
+            for q, n in enumerate(sizes):
+                model = ("fr", "sym")[q % 2]
+                _, prm, d = inputs(model, n, 400 + q)
+                delta = torch.zeros(n ** 3 + 1, dtype=torch.float32, device=DEV)[off:off + n ** 3]
+                delta.copy_(torch.from_numpy(d.ravel()))
+                boxes.append(dict(n=n, model=model, params=prm, delta=delta.view(n, n, n),
+                                  field=torch.empty((n, n, n), dtype=torch.float64, device=DEV),
+                                  force=torch.empty((3, n, n, n), device=DEV)))
+            print("boxes in the smaller pool", sizes, refused, off, flush=True)
+            st = mg.solve_batched(boxes, tol=1e-8)
+            assert all(s.status == 0 and s.rel_resid <= 1e-8 for s in st)
+            got.append([(b["field"], b["force"]) for b in boxes])
+        mg.close()
+    for small, plain in zip(got[:3], got[3:]):
+        for a, b in zip(small, plain):
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
