@@ -116,20 +116,24 @@ typedef struct mg_ctx mg_ctx;
  * MGGPU_PROLONG_SMOOTH_KT sets the coarse planes per workgroup (default 8;
  * 0 runs prolongation and half-sweep as separate kernels; identical
  * results) of the kernel that forms the prolonged correction inside the
- * first post-smoothing half-sweep of the f(R), symmetron and linear
- * (adjoint) FP32 cycles, used on the levels where its grid reaches
+ * first post-smoothing half-sweep of the f(R) and linear (adjoint) FP32
+ * cycles, used on the levels where its grid reaches
  * MGGPU_PROLONG_SMOOTH_MIN_BLOCKS workgroups (default 512; the depth is
  * halved to reach it),
  * MGGPU_MID_MAX_N sets up to how many cells a side a level of the f(R),
- * symmetron and adjoint FP32 V(1,1) cycles runs its way down and its way up in
- * one launch each (default and maximum 80; 0: separate kernels; identical
- * results), and
+ * symmetron and adjoint FP32 cycles with one sweep before and one after
+ * coarsening (nu_pre = nu_post = 1; V, F and W) runs its way down and its way
+ * up in one launch each (default and maximum 80; 0: separate kernels;
+ * identical results), and
  * MGGPU_FP16_STORAGE=0 keeps the finest level's X and rho of the
  * FP32-refined solve in FP32 instead of 16-bit floats (default 1; n % 8 == 0
  * grids; changes rounding inside the FP32 correction cycles only, the FP64
  * residual and the solution's tolerance are unaffected).  MGGPU_CIC_DIRECT=1
  * makes cic_assign always take its direct atomic path, 0 its binned path
- * (identical results; by default the faster one for the particles and cells).
+ * where memory allows (identical results; by default the faster one for the
+ * particles and cells).  MGGPU_TEST_BATCH_POOL = s refuses batched solves
+ * workspaces of s bytes or more (a test hook: those that leave out optional
+ * buffers are then used).
  * Returns MG_EINVAL for a bad n or NULL out. */
 int mg_ctx_create(mg_ctx **out, int n, void *hip_stream);
 void mg_ctx_destroy(mg_ctx *ctx);
@@ -188,7 +192,7 @@ int mg_solve(mg_ctx *ctx, int model, const mg_model_params *params,
  * hipFree or other allocating routine, and the context must only have been
  * created (mg_ctx_create, which allocates its few scalars, at set-up).
  * Limit: the workspace of an n^3 solve must fit the array, which holds
- * n <= 64 (about 15 MB at n = 64); larger n returns MG_EINVAL.  Every call
+ * n <= 64 (16.2 MB at n = 64); larger n returns MG_EINVAL.  Every call
  * on one GPU shares that GPU's array, whatever the context or stream, and
  * leaves its contents behind (the solve reads nothing it has not written):
  * calls that overlap on one GPU race. */

@@ -2734,8 +2734,8 @@ __global__ __launch_bounds__(kFusedThreads) void k_fused_lin(FusedLin<T> F, Fuse
 // differ by constants; and a coarsest level of at most 10^3 has one cell per
 // thread, 4^3 on one wave, which needs no barrier.  A launch at 16^3, 8^3, 4^3
 // (8 coarsest sweeps) takes 26 us (f(R)), 31 (CQ), 43 (symmetron), 21 (linear,
-// FP32) and 42 (f(R), FP64) against 41, 52, 63, 38 and 94 on global memory; a
-// coarsest 10^3 in FP64 (200 sweeps) 330 against 761.  What bounds it now is
+// FP32) and 43 (f(R), FP64) against 41, 52, 63, 38 and 94 on global memory; a
+// coarsest 10^3 in FP64 (200 sweeps) 296 against 761.  What bounds it now is
 // the dependent chain of a phase and, on 16^3, one compute unit's issue rate.
 // Larger coarsest levels (18^3, 22^3, ...) stay with the kernels above.
 // ---------------------------------------------------------------------------

@@ -18,10 +18,11 @@
 //
 // Down / up take 5.0 / 4.8 us at 32^3 (f(R); 256 threads: 7.6 / 6.5) against 17 /
 // 15 for the separate kernels and 7.3 / 7.1 against 18 / 16 at 64^3 (symmetron),
-// where the launch and four dependent phases bound them.  Recomputation makes a
-// tile cost 2.6 times its own half-sweeps, and from 96^3 on that eats the gain
-// (96^3: 22 / 20 against 21 / 19 us, 128^3: 30 / 31 against 26 / 22), so the
-// kernels are used up to kMidMaxN cells a side.
+// where the launch and four dependent phases bound them.  Recomputation makes the
+// way down solve 52 + 32 rows of cells for its 16 + 16 (2.6 times), the way up
+// 32 + 16 (1.5 times) after prolonging 52 rows for 16 (3.25 times), and from 96^3
+// on that eats the gain (96^3: 22 / 20 against 21 / 19 us, 128^3: 30 / 31 against
+// 26 / 22), so the kernels are used up to kMidMaxN cells a side.
 #pragma once
 #include "mg_kernels.h"
 

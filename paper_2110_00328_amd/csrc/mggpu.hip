@@ -1253,7 +1253,8 @@ int cycle32(mg_ctx* ctx, const Consts& C, const mg_solver_opts* o, int l, int ty
   }
   // f(R) only: the symmetron's closed form, inlined for each of the kernel's 16
   // cells, makes it slower than the two kernels (77 us against 15 + 30 at
-  // 256^3 with clumps)
+  // 256^3 with clumps; solves of 128^3 to 512^3, with clumps or none, got no
+  // slower when it went)
   if constexpr (M == FR)
     if (vec && fuse_prolong(ctx, l)) {
       // e += P e_H formed inside the first colour-0 half-sweep
@@ -4087,10 +4088,12 @@ void g_smooth(mg_ctx* ctx, hipStream_t st, const GClass& K, const Lev& L, int it
 // a single box): up to kGMidTiles tiles in a launch; above, the tiles'
 // recomputation costs more than the launches they save (64 boxes of
 // 64^3-128^3: 10.5 ms without, 10.05 with 800, 11.4 with 3000; 12 of
-// 32^3-64^3: 2.8 / 2.2 / 2.25)
+// 32^3-64^3: 2.8 / 2.2 / 2.25).  With and without, ms: 6 of 48^3 0.95 / 1.32, 4 of
+// 64^3 0.98 / 1.31, 36 of 32^3-48^3 3.9 / 4.6, 24 of 48^3-64^3 8.1 / 8.9, 24 of
+// 56^3 6.8 / 6.9, 48 of 32^3 1.28 / 1.27.
 constexpr unsigned kGMidTiles = 800;
 bool g_use_mid(const mg_ctx* ctx, const GClass& K, const Lev* L, const mg_solver_opts* o, int l) {
-  return g_mid_level(ctx, K, L, l) && o->nu_pre == 1 && o->nu_post == 1 && 
+  return g_mid_level(ctx, K, L, l) && o->nu_pre == 1 && o->nu_post == 1 &&
          mid_blocks(L[l]) * (unsigned)K.count <= kGMidTiles;
 }
 
