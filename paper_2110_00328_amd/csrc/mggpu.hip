@@ -3075,32 +3075,41 @@ int cic_rounds(int64_t np, int64_t ntiles) {
   while (r > 1 && np < (int64_t)512 * kCicRound * r) r /= 2;
   return r;
 }
-// The binned path's buffers for np particles, one allocation; false without
-// memory for them.  Larger ones are added for a larger deposit: a graph captured
-// from an earlier one still uses the earlier buffers, so those live until the
-// context's end.  From the second time on half as much again is taken, so that
-// deposits that keep growing add few.
+// The binned path's buffers for np particles, one allocation, which on sides that
+// hold both paths' buffers (cic_makes_both) also makes the direct path's (an
+// allocation of this size costs the host 10-40 us).  False without memory for
+// them.  Larger ones are added for a larger deposit: a graph captured from an
+// earlier one still uses the earlier buffers, so those live until the context's
+// end.  From the second time on half as much again is taken, so that deposits
+// that keep growing add few.
 bool cic_buffers(mg_ctx* ctx, int64_t np, int64_t ntiles) {
   if (ctx->cic_np >= np) return true;
   auto up = [](int64_t b) { return (b + 255) & ~(int64_t)255; };
   const std::string err = ctx->err;
-  for (int64_t cap = std::max(np, ctx->cic_np + ctx->cic_np / 2);; cap = np) {
+  int64_t cap = std::max(np, ctx->cic_np + ctx->cic_np / 2);
+  bool both = ctx->cic_direct < 0 && cic_makes_both(ctx->n) && !ctx->cic;
+  for (;;) {
     const int64_t nbp = (cap + kCicRound - 1) / kCicRound;
     const int64_t rec = up((nbp * kCicRound + kCicRounds * kCicRound) * (int64_t)sizeof(uint2));
     const int64_t runs = up(cap * (int64_t)sizeof(unsigned long long));
     const int64_t nrec = up(nbp * (int64_t)sizeof(uint32_t));
+    const int64_t cnt = up(3 * 8 * ntiles * (int64_t)sizeof(uint32_t));
+    const int64_t acc = both ? cells(ctx->L[0]) * (int64_t)sizeof(int64_t) : 0;
     char* base = nullptr;
-    if (dalloc(ctx, &base, rec + runs + nrec + 3 * 8 * ntiles * (int64_t)sizeof(uint32_t)) == MG_OK) {
+    if (dalloc(ctx, &base, rec + runs + nrec + cnt + acc) == MG_OK) {
       ctx->cic_rec = (uint2*)base;
       ctx->cic_runs = (unsigned long long*)(base + rec);
       ctx->cic_nrec = (uint32_t*)(base + rec + runs);
       ctx->cic_cnt = (uint32_t*)(base + rec + runs + nrec);
+      if (both) ctx->cic = (int64_t*)(base + rec + runs + nrec + cnt);
       ctx->cic_np = cap;
       return true;
     }
     (void)hipGetLastError();
     ctx->err = err;
-    if (cap == np) return false;
+    if (cap == np && !both) return false;
+    if (cap == np) both = false;
+    cap = np;
   }
 }
 
@@ -3136,7 +3145,6 @@ int cic_assign(mg_ctx* ctx, const float* pos, int64_t np, float* delta_out) {
     if (binned && !have_b && have_d && hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess)
       (void)hipGetLastError();
     binned = cic_takes_binned(binned, have_b, have_d, cap != hipStreamCaptureStatusNone);
-    if (binned && cic_makes_both(n)) (void)cic_accumulator(ctx);
   }
   if (binned) binned = cic_buffers(ctx, np, ntiles);
   if (!binned && !cic_accumulator(ctx)) {
